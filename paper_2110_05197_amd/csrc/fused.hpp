@@ -72,6 +72,28 @@ constexpr int fused_lds_bytes()
            + NComp<MODEL>::n * L::Q * TX * TY * (int)sizeof(typename Prec<PR>::C);
 }
 
+// Spreading the loads of plane z+2 over the collision of plane z: vector
+// instructions between two loads, 0 = all loads first.  One block fills a
+// compute unit, its waves run in step from barrier to barrier, and 38 loads in
+// a row from each of them reach memory as one burst per plane.  256^3 FP32
+// colour gradient, ms per step, first 1.082, every 6 instructions 1.11,
+// 14 1.06, 20 1.07, 22 1.14 (64-bit addressing, whose address arithmetic
+// spaces the loads a little by itself: 1.115); SC multiphase 0.488 first,
+// 0.470 every 14; 256^3 FP16 storage 0.658 first, 0.61 every 30.  Not where
+// registers are short or the arithmetic is FP64 (128^3 FP64 0.293 first,
+// 0.302 every 12; mixed 256^3 1.12 and 1.20), nor for the two-component
+// Shan-Chen model (0.597 and 0.600 at 128 x 128 x 512), nor the 2-D rows (two
+// blocks a compute unit, 18 loads; 4096^2 FP32 0.494 and 0.490).
+template <int PR, int MODEL, bool YH>
+constexpr int kLoadSpacing = !YH ? 0 : PR == 1 && MODEL != SC_MC ? 14 : PR == 3 && MODEL == CG ? 30 : 0;
+
+// Kernels that read through 64-bit pointers although their stores are buffer
+// accesses: the address arithmetic between the loads keeps them from leaving
+// in one burst where kLoadSpacing does not.  4096^2 FP32 rows: 0.480 ms,
+// 0.494 with buffer loads; mixed columns, 96 x 96 x 384 with walls and
+// outflow: 0.348 and 0.383, 256^3 1.12 and 1.15.
+template <int PR, bool YH> constexpr bool kPointerLoads = (PR == 1 && !YH) || (PR == 2 && YH);
+
 // One block's work: the TX x TY column at (x0, y0), planes [z0, z1).  An
 // EDGE column is the last one in x when TX does not divide nx: its first
 // w = nx - x0 threads hold nodes, the others only take part in the barriers,
@@ -83,11 +105,11 @@ constexpr int fused_lds_bytes()
 // (kConsNever / kConsAsked / kConsAlways, see cg_collide): the batched
 // kernels ask each simulation, the solo launches choose a kernel.
 template <int PR, int MODEL, int TX, int TY, bool PERIODIC, bool EDGE = false, class L = D3Q19, class LA = L,
-          int CONS = kConsShared<PR>>
-__device__ __forceinline__ void fused_column(const KParams &P, const typename Prec<PR>::S *__restrict__ src,
-                                             typename Prec<PR>::S *__restrict__ dst, unsigned *flag, int x0, int y0,
-                                             int z0, int z1, unsigned char *smem)
+          int CONS = kConsShared<PR>, bool FAR = false>
+__device__ __forceinline__ void fused_column(const KParams &P, const void *srcp, void *dstp, unsigned *flag, int x0,
+                                             int y0, int z0, int z1, unsigned char *smem)
 {
+    using S = typename Prec<PR>::S;
     using C = typename Prec<PR>::C;
     using M = typename Prec<PR>::M;
     using FT = typename Prec<PR>::F;
@@ -106,8 +128,9 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
     FT (*lds)[NF][PL] = reinterpret_cast<FT (*)[NF][PL]>(smem);
     C *pop = reinterpret_cast<C *>(smem + fused_ring_bytes<LA, MODEL, TX, TY, FT>());
 
-    const long long SW = P.S;
     const int nx = P.nx, ny = P.ny, nz = P.nz;
+    const Pops<L, K, S, FAR || kPointerLoads<PR, YH>> src(srcp, P);
+    const Pops<L, K, S, FAR> dst(dstp, P);
     const HP<C, M> H = make_hp<C, M>(P);
     const int tid = threadIdx.x;
     const int lx = tid % TX, ly = tid / TX;
@@ -128,9 +151,9 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
     const int h_slot = (hy + RY) * HX + (hx + 1);
     const int hgx = stencil_coord(x0 + hx, nx, P.bc[0]);
     const int hgy = stencil_coord(y0 + hy, ny, P.bc[1]);
-    const long long n_xy = (long long)x + (long long)nx * y;
-    const long long h_xy = (long long)hgx + (long long)nx * hgy;
-    const long long sxy = (long long)nx * ny;
+    const unsigned n_xy = (unsigned)x + (unsigned)nx * (unsigned)y;   // N < 2^31
+    const unsigned h_xy = (unsigned)hgx + (unsigned)nx * (unsigned)hgy;
+    const unsigned sxy = (unsigned)nx * (unsigned)ny;
     auto ring = [&](int p) { return (p - z0 + 1) & 3; };
 
     bool bad = false;
@@ -146,7 +169,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
             bad = bad || node_bad(r, jv[0] + jv[1] + jv[2]);
         }
     };
-    auto zoff = [&](int p) { return sxy * stencil_coord(p, nz, P.bc[2]); };
+    auto zoff = [&](int p) { return sxy * (unsigned)stencil_coord(p, nz, P.bc[2]); };
 
     C c[K][Q];                  // populations of plane z (plane z+1's wait in LDS)
     M drc[2], jc[3], drn[2], jn[3];
@@ -155,11 +178,11 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
         C tmp[K][Q];
         M d2[2], j2[3];
         if (act) {
-            load_node<L, K>(src, SW, n_xy + zoff(z0 - 1), tmp);
+            load_node(src, n_xy + zoff(z0 - 1), tmp);
             put(z0 - 1, my_slot, tmp, d2, j2, true);
-            load_node<L, K>(src, SW, n_xy + zoff(z0), c);
+            load_node(src, n_xy + zoff(z0), c);
             put(z0, my_slot, c, drc, jc, true);
-            load_node<L, K>(src, SW, n_xy + zoff(z0 + 1), tmp);
+            load_node(src, n_xy + zoff(z0 + 1), tmp);
             put(z0 + 1, my_slot, tmp, drn, jn, true);
 #pragma unroll
             for (int k = 0; k < K; ++k)
@@ -168,31 +191,33 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
         }
         if (has_h)
             for (int p = z0 - 1; p <= z0 + 1; ++p) {
-                load_node<L, K>(src, SW, h_xy + zoff(p), tmp);
+                load_node(src, h_xy + zoff(p), tmp);
                 put(p, h_slot, tmp, d2, j2, false);
             }
     }
     __syncthreads();
 
     for (int z = z0; z < z1; ++z) {
-        // 1. issue the loads of plane z+2 (consumed after the collision).  The
-        // 2-D row kernel issues them at raised wave priority, so that they
-        // leave before the SIMD's other waves take the issue slots for their
-        // arithmetic: 4096^2 FP32 0.489 -> 0.480 ms.  The D3Q19 column
-        // kernel ran 2 % slower with it (1.115 -> 1.134-1.151 ms at 256^3),
-        // and raised priority around the stores cost 1.5 % in a timing copy.
-        constexpr bool prio = !YH;
+        // 1. issue the loads of plane z+2 (consumed after the collision): the
+        // halo ring's here; the tile's here too, or spread over the collision
+        // (kLoadSpacing).  Raised wave priority lets them leave before the
+        // SIMD's other waves take the issue slots for their arithmetic: 2-D
+        // rows 4096^2 FP32 0.489 -> 0.480 ms, buffer loads at 256^3 FP32 1.155
+        // -> 1.085 ms, 64-bit addressed columns on ragged rows 234 x 80 x 119
+        // FP32 0.223 -> 0.217.
+        constexpr int spacing = FAR ? 0 : kLoadSpacing<PR, MODEL, YH>;
         const bool ahead = z + 2 <= z1;
-        RawNode<L, K, typename Prec<PR>::S, C> dr_, hr_;
-        if constexpr (prio) __builtin_amdgcn_s_setprio(3);
+        RawNode<L, K, S, C> dr_, hr_;
+        __builtin_amdgcn_s_setprio(3);
         if (ahead) {
-            if (act) dr_.load(src, SW, n_xy + zoff(z + 2));
-            if (has_h) hr_.load(src, SW, h_xy + zoff(z + 2));
+            if (spacing == 0 && act) dr_.load(src, n_xy + zoff(z + 2));
+            if (has_h) hr_.load(src, h_xy + zoff(z + 2));
         }
-        if constexpr (prio) __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_s_setprio(0);
 
         // 2. collide plane z with the stencil values of planes z-1, z, z+1
         if (act) {
+            if constexpr (spacing > 0) dr_.load(src, ahead ? n_xy + zoff(z + 2) : kNoNode);
             C v[NF][Q];
 #pragma unroll
             for (int i = 1; i < Q; ++i) {
@@ -242,13 +267,22 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
                 sc_collide_component<L, C, M>(c[0], H.om[0], drc[0], rR, u, FR, H.rho0[0], H.corrM[0], H.shiftM[0]);
                 sc_collide_component<L, C, M>(c[K - 1], H.om[1], drc[1], rB, u, FB, H.rho0[1], H.corrM[1], H.shiftM[1]);
             }
-            const long long n = n_xy + sxy * z;
+            const unsigned n = n_xy + sxy * (unsigned)z;
             // populations that stay on their x (cx = 0) land on whole cache
             // lines and are never read again in this step: stream them past
             // the cache; the x-shifted ones share lines with the neighbouring
             // tile's stores and go through L2
-            if constexpr (PERIODIC) push_store_periodic<LA, K, typename Prec<PR>::S, C, true>(P, dst, x, y, z, n, c);
-            else push_store_general<LA, K, typename Prec<PR>::S, C, true>(P, dst, x, y, z, n, c);
+            if constexpr (PERIODIC) push_store_periodic<LA, true>(P, dst, x, y, z, n, c);
+            else push_store_general<LA, true>(P, dst, x, y, z, n, c);
+            // the order asked of the scheduler: one load, then `spacing`
+            // vector instructions of the collision, and so on
+            if constexpr (spacing > 0) {
+#pragma unroll
+                for (int q = 0; q < RawNode<L, K, S, C>::KA * Q; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, spacing, 0);
+                }
+            }
         }
 
         // 3. stencil values of plane z+2
@@ -283,11 +317,12 @@ __device__ __forceinline__ void fused_column(const KParams &P, const typename Pr
     if (any != 0ull && (tid & 63) == 0) atomicOr(flag, 1u);
 }
 
-// RAGGED: TX does not divide nx, and the last column in x is an edge column.
-template <int PR, int MODEL, int TX, int TY, bool PERIODIC, bool RAGGED, class L = D3Q19, class LA = L,
-          bool CONS = false>
-__global__ __launch_bounds__(TX *TY) void k_fused(KParams P, const typename Prec<PR>::S *__restrict__ src,
-                                                  typename Prec<PR>::S *__restrict__ dst, unsigned *flag, int TZ,
+// The columns of a launch in x: all full (TX divides nx), the last one an edge
+// column, or one edge column only (nx < TX; a kernel of its own holds a single
+// column body: 27 x 32 x 230 mixed 0.0385 -> 0.0362 ms).
+constexpr int kColsFull = 0, kColsRagged = 1, kColsNarrow = 2;
+template <int PR, int MODEL, int TX, int TY, bool PERIODIC, int COLS, class L, class LA, bool CONS, bool FAR>
+__global__ __launch_bounds__(TX *TY) void k_fused(KParams P, const void *src, void *dst, unsigned *flag, int TZ,
                                                   int tiles_x, int tiles_y)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -295,13 +330,13 @@ __global__ __launch_bounds__(TX *TY) void k_fused(KParams P, const typename Prec
     const int bx = t % tiles_x, by = (t / tiles_x) % tiles_y, bz = t / (tiles_x * tiles_y);
     const int x0 = bx * TX, y0 = by * TY, z0 = bz * TZ, z1 = min(z0 + TZ, P.nz);
     constexpr int cons = CONS ? kConsAlways : kConsNever;
-    if constexpr (RAGGED) {
-        if (bx == tiles_x - 1) {
-            fused_column<PR, MODEL, TX, TY, PERIODIC, true, L, LA, cons>(P, src, dst, flag, x0, y0, z0, z1, smem);
+    if constexpr (COLS != kColsFull) {
+        if (COLS == kColsNarrow || bx == tiles_x - 1) {
+            fused_column<PR, MODEL, TX, TY, PERIODIC, true, L, LA, cons, FAR>(P, src, dst, flag, x0, y0, z0, z1, smem);
             return;
         }
     }
-    fused_column<PR, MODEL, TX, TY, PERIODIC, false, L, LA, cons>(P, src, dst, flag, x0, y0, z0, z1, smem);
+    fused_column<PR, MODEL, TX, TY, PERIODIC, false, L, LA, cons, FAR>(P, src, dst, flag, x0, y0, z0, z1, smem);
 }
 
 // Batched one-pass step: the blocks of all eligible simulations of a group
@@ -351,10 +386,12 @@ constexpr int batch_tile_ty(int precision, int model, int nx, int ny)
 // a multiple of 64 or not (EDGE), or on 96 x 4 columns (WIDE)
 constexpr int kFusedPeriodic = 1, kFusedBounded = 2, kFusedPeriodicEdge = 4, kFusedBoundedEdge = 8;
 constexpr int kFusedPeriodicWide = 16, kFusedBoundedWide = 32;
-constexpr int fused_kind(bool periodic, bool edge, bool wide)
+constexpr int kFusedFar = 6;   // the same kinds, 64-bit addressing: bits 6 .. 11
+constexpr int fused_kind(bool periodic, bool edge, bool wide, bool far)
 {
-    return wide ? (periodic ? kFusedPeriodicWide : kFusedBoundedWide)
-           : edge ? (periodic ? kFusedPeriodicEdge : kFusedBoundedEdge) : (periodic ? kFusedPeriodic : kFusedBounded);
+    const int k = wide ? (periodic ? kFusedPeriodicWide : kFusedBoundedWide)
+                  : edge ? (periodic ? kFusedPeriodicEdge : kFusedBoundedEdge) : (periodic ? kFusedPeriodic : kFusedBounded);
+    return far ? k << kFusedFar : k;
 }
 
 __device__ __forceinline__ int find_sim_fused(const SimDesc *D, int n, long long b)
@@ -370,7 +407,7 @@ __device__ __forceinline__ int find_sim_fused(const SimDesc *D, int n, long long
 constexpr int kb_tx(bool wide) { return wide ? kBatchWideTX : kBatchTX; }
 constexpr int kb_ty(int precision, bool wide) { return wide ? kBatchWideTY : batch_ty(precision); }
 
-template <int PR, int MODEL, bool PERIODIC, bool EDGE, bool WIDE = false>
+template <int PR, int MODEL, bool PERIODIC, bool EDGE, bool WIDE = false, bool FAR = false>
 __global__ __launch_bounds__(kb_tx(WIDE) * kb_ty(PR, WIDE)) void kb_fused(SimDesc *D, int nsims)
 {
     static_assert(!(WIDE && EDGE) && !(WIDE && !batch_wide_kernel(PR, MODEL)), "96-wide columns: full columns");
@@ -378,7 +415,7 @@ __global__ __launch_bounds__(kb_tx(WIDE) * kb_ty(PR, WIDE)) void kb_fused(SimDes
     extern __shared__ __align__(16) unsigned char smem[];
     const int s = find_sim_fused(D, nsims, blockIdx.x);
     const SimDesc &d = D[s];
-    if (d.state != 0) return;
+    if (d.state != 0 || (d.P.far_rows != 0) != FAR) return;
     if ((d.P.bc[0] == 0 && d.P.bc[1] == 0 && d.P.bc[2] == 0) != PERIODIC) return;
     if (batch_wide(PR, MODEL, d.P.nx, d.P.ny) != WIDE) return;
     if (!WIDE && (d.P.nx % kBatchTX != 0) != EDGE) return;
@@ -386,11 +423,9 @@ __global__ __launch_bounds__(kb_tx(WIDE) * kb_ty(PR, WIDE)) void kb_fused(SimDes
     const int tiles_x = (d.P.nx + TX - 1) / TX, tiles_y = d.P.ny / TY;
     const int bx = (int)(b % tiles_x), by = (int)((b / tiles_x) % tiles_y), bz = (int)(b / ((long long)tiles_x * tiles_y));
     const int x0 = bx * TX, y0 = by * TY, z0 = bz * d.ftz, z1 = min(z0 + d.ftz, d.P.nz);
-    using S = typename Prec<PR>::S;
-    const S *src = global_ptr<const S>(d.f[d.cur]);
-    S *dst = global_ptr<S>(d.f[d.cur ^ 1]);
     unsigned *flag = global_ptr<unsigned>(d.flag);
-    fused_column<PR, MODEL, TX, TY, PERIODIC, EDGE>(d.P, src, dst, flag, x0, y0, z0, z1, smem);
+    fused_column<PR, MODEL, TX, TY, PERIODIC, EDGE, D3Q19, D3Q19, kConsShared<PR>, FAR>(
+        d.P, global_ptr<char>(d.f[d.cur]), global_ptr<char>(d.f[d.cur ^ 1]), flag, x0, y0, z0, z1, smem);
 }
 
 // Planes per column of the batched simulations of a group.  A column
@@ -466,38 +501,36 @@ long long batch_fused_resident()
 // kinds: the fused_kind() bits of the simulations present.  Every launch
 // covers the group's whole one-pass block range; a block whose simulation is
 // of another kind returns at once.
+template <int PR, int MODEL, bool PERIODIC, bool EDGE, bool WIDE, bool FAR>
+void launch_batch_kind(SimDesc *D, int n, long long fblocks, int kinds, hipStream_t s)
+{
+    if (!(kinds & fused_kind(PERIODIC, EDGE, WIDE, FAR))) return;
+    constexpr int TX = kb_tx(WIDE), TY = kb_ty(PR, WIDE), lds = fused_lds_bytes<PR, MODEL, TX, TY>();
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void *)kb_fused<PR, MODEL, PERIODIC, EDGE, WIDE, FAR>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((kb_fused<PR, MODEL, PERIODIC, EDGE, WIDE, FAR>), dim3((unsigned)fblocks), dim3(TX * TY), lds, s, D, n);
+}
+template <int PR, int MODEL, bool FAR>
+void launch_batch_kinds(SimDesc *D, int n, long long fblocks, int kinds, hipStream_t s)
+{
+    launch_batch_kind<PR, MODEL, true, false, false, FAR>(D, n, fblocks, kinds, s);
+    launch_batch_kind<PR, MODEL, false, false, false, FAR>(D, n, fblocks, kinds, s);
+    launch_batch_kind<PR, MODEL, true, true, false, FAR>(D, n, fblocks, kinds, s);
+    launch_batch_kind<PR, MODEL, false, true, false, FAR>(D, n, fblocks, kinds, s);
+    if constexpr (batch_wide_kernel(PR, MODEL)) {
+        launch_batch_kind<PR, MODEL, true, false, true, FAR>(D, n, fblocks, kinds, s);
+        launch_batch_kind<PR, MODEL, false, false, true, FAR>(D, n, fblocks, kinds, s);
+    }
+}
 template <int PR, int MODEL>
 void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStream_t s)
 {
-    constexpr int lds = fused_lds_bytes<PR, MODEL, kBatchTX, batch_ty(PR)>();
-    const void *fns[4] = {(const void *)kb_fused<PR, MODEL, true, false>, (const void *)kb_fused<PR, MODEL, false, false>,
-                          (const void *)kb_fused<PR, MODEL, true, true>, (const void *)kb_fused<PR, MODEL, false, true>};
-    static bool attr_set = false;
-    if (!attr_set) {
-        for (const void *fn : fns) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr_set = true;
-    }
-    const dim3 grid((unsigned)fblocks), block(kBatchTX * batch_ty(PR));
-    if (kinds & kFusedPeriodic) hipLaunchKernelGGL((kb_fused<PR, MODEL, true, false>), grid, block, lds, s, D, n);
-    if (kinds & kFusedBounded) hipLaunchKernelGGL((kb_fused<PR, MODEL, false, false>), grid, block, lds, s, D, n);
-    if (kinds & kFusedPeriodicEdge) hipLaunchKernelGGL((kb_fused<PR, MODEL, true, true>), grid, block, lds, s, D, n);
-    if (kinds & kFusedBoundedEdge) hipLaunchKernelGGL((kb_fused<PR, MODEL, false, true>), grid, block, lds, s, D, n);
-    if constexpr (batch_wide_kernel(PR, MODEL)) {
-        constexpr int lds_w = fused_lds_bytes<PR, MODEL, kBatchWideTX, kBatchWideTY>();
-        static bool attr_w = false;
-        if (!attr_w) {
-            (void)hipFuncSetAttribute((const void *)kb_fused<PR, MODEL, true, false, true>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_w);
-            (void)hipFuncSetAttribute((const void *)kb_fused<PR, MODEL, false, false, true>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_w);
-            attr_w = true;
-        }
-        const dim3 block_w(kBatchWideTX * kBatchWideTY);
-        if (kinds & kFusedPeriodicWide)
-            hipLaunchKernelGGL((kb_fused<PR, MODEL, true, false, true>), grid, block_w, lds_w, s, D, n);
-        if (kinds & kFusedBoundedWide)
-            hipLaunchKernelGGL((kb_fused<PR, MODEL, false, false, true>), grid, block_w, lds_w, s, D, n);
-    }
+    launch_batch_kinds<PR, MODEL, false>(D, n, fblocks, kinds, s);
+    if (kinds >> kFusedFar) launch_batch_kinds<PR, MODEL, true>(D, n, fblocks, kinds, s);
 }
 
 struct FusedShape {
@@ -533,41 +566,63 @@ inline bool fused_shape(const KParams &P, FusedShape &sh, bool wide = false)
     return true;
 }
 
-template <int PR, int MODEL, int TX, int TY, bool RAGGED, bool CONS>
-void launch_fused_kernel(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, hipStream_t s)
+// One launch of k_fused; the dynamic-LDS limit is raised once per kernel and
+// process.
+template <int PR, int MODEL, int TX, int TY, bool PERIODIC, int COLS, class L, class LA, bool CONS, bool FAR>
+void launch_fused_one(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, int tiles_x, int tiles_y,
+                      hipStream_t s)
 {
-    const int tiles_x = (P.nx + TX - 1) / TX, tiles_y = P.ny / TY, tiles_z = (P.nz + tz - 1) / tz;
-    const dim3 grid(tiles_x * tiles_y * tiles_z), block(TX * TY);
-    using S = typename Prec<PR>::S;
-    constexpr int lds = fused_lds_bytes<PR, MODEL, TX, TY>();
-    static bool attr_set = false;   // raise the dynamic-LDS limit once per process
+    constexpr int lds = fused_lds_bytes<PR, MODEL, TX, TY, LA>();
+    static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)k_fused<PR, MODEL, TX, TY, true, RAGGED, D3Q19, D3Q19, CONS>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        (void)hipFuncSetAttribute((const void *)k_fused<PR, MODEL, TX, TY, false, RAGGED, D3Q19, D3Q19, CONS>,
+        (void)hipFuncSetAttribute((const void *)k_fused<PR, MODEL, TX, TY, PERIODIC, COLS, L, LA, CONS, FAR>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         attr_set = true;
     }
-    if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0)
-        hipLaunchKernelGGL((k_fused<PR, MODEL, TX, TY, true, RAGGED, D3Q19, D3Q19, CONS>), grid, block, lds, s, P,
-                           (const S *)src, (S *)dst, flag, tz, tiles_x, tiles_y);
+    const dim3 grid(tiles_x * tiles_y * ((P.nz + tz - 1) / tz)), block(TX * TY);
+    hipLaunchKernelGGL((k_fused<PR, MODEL, TX, TY, PERIODIC, COLS, L, LA, CONS, FAR>), grid, block, lds, s, P, src, dst,
+                       flag, tz, tiles_x, tiles_y);
+}
+template <int PR, int MODEL, int TX, int TY, int COLS, class L, class LA, bool CONS>
+void launch_fused_bc(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, int tiles_x, int tiles_y,
+                     hipStream_t s)
+{
+    const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
+    if (periodic && !P.far_rows)
+        launch_fused_one<PR, MODEL, TX, TY, true, COLS, L, LA, CONS, false>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+    else if (periodic)
+        launch_fused_one<PR, MODEL, TX, TY, true, COLS, L, LA, CONS, true>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+    else if (!P.far_rows)
+        launch_fused_one<PR, MODEL, TX, TY, false, COLS, L, LA, CONS, false>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
     else
-        hipLaunchKernelGGL((k_fused<PR, MODEL, TX, TY, false, RAGGED, D3Q19, D3Q19, CONS>), grid, block, lds, s, P,
-                           (const S *)src, (S *)dst, flag, tz, tiles_x, tiles_y);
+        launch_fused_one<PR, MODEL, TX, TY, false, COLS, L, LA, CONS, true>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+}
+template <int PR, int MODEL, int TX, int TY, int COLS, bool CONS>
+void launch_fused_kernel(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, hipStream_t s)
+{
+    launch_fused_bc<PR, MODEL, TX, TY, COLS, D3Q19, D3Q19, CONS>(P, src, dst, flag, tz, (P.nx + TX - 1) / TX, P.ny / TY, s);
 }
 
 // The mass-keeping collision has kernels of its own, so that the default
 // step carries none of it.
-template <int PR, int MODEL, int TX, int TY, bool RAGGED>
+template <int PR, int MODEL, int TX, int TY, int COLS>
 void launch_fused_shape(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, hipStream_t s)
 {
     if constexpr (kConserveRest<PR> && MODEL == CG) {
         if (P.conserve) {
-            launch_fused_kernel<PR, MODEL, TX, TY, RAGGED, true>(P, src, dst, flag, tz, s);
+            launch_fused_kernel<PR, MODEL, TX, TY, COLS, true>(P, src, dst, flag, tz, s);
             return;
         }
     }
-    launch_fused_kernel<PR, MODEL, TX, TY, RAGGED, false>(P, src, dst, flag, tz, s);
+    launch_fused_kernel<PR, MODEL, TX, TY, COLS, false>(P, src, dst, flag, tz, s);
+}
+
+template <int PR, int MODEL, int TY>
+void launch_fused_cols(const KParams &P, const FusedShape &sh, const void *src, void *dst, unsigned *flag, hipStream_t s)
+{
+    if (!sh.ragged) launch_fused_shape<PR, MODEL, 64, TY, kColsFull>(P, src, dst, flag, sh.tz, s);
+    else if (P.nx > 64) launch_fused_shape<PR, MODEL, 64, TY, kColsRagged>(P, src, dst, flag, sh.tz, s);
+    else launch_fused_shape<PR, MODEL, 64, TY, kColsNarrow>(P, src, dst, flag, sh.tz, s);
 }
 
 template <int PR, int MODEL>
@@ -577,17 +632,12 @@ void launch_fused(const KParams &P, const void *src, void *dst, unsigned *flag, 
     fused_shape(P, sh, PR == 0);  // checked at create time
     if constexpr (PR != 0) {
         if (sh.tx == 96) {
-            launch_fused_shape<PR, MODEL, 96, 4, false>(P, src, dst, flag, sh.tz, s);
+            launch_fused_shape<PR, MODEL, 96, 4, kColsFull>(P, src, dst, flag, sh.tz, s);
             return;
         }
     }
-    if (sh.ty == 4) {
-        if (sh.ragged) launch_fused_shape<PR, MODEL, 64, 4, true>(P, src, dst, flag, sh.tz, s);
-        else launch_fused_shape<PR, MODEL, 64, 4, false>(P, src, dst, flag, sh.tz, s);
-    } else if constexpr (PR != 0) {
-        if (sh.ragged) launch_fused_shape<PR, MODEL, 64, 8, true>(P, src, dst, flag, sh.tz, s);
-        else launch_fused_shape<PR, MODEL, 64, 8, false>(P, src, dst, flag, sh.tz, s);
-    }
+    if (sh.ty == 4) launch_fused_cols<PR, MODEL, 4>(P, sh, src, dst, flag, s);
+    else if constexpr (PR != 0) launch_fused_cols<PR, MODEL, 8>(P, sh, src, dst, flag, s);
 }
 
 // D2Q9 one-pass step: the 2-D box as nx x 1 x ny (neighbours placed by
@@ -615,28 +665,12 @@ inline void fused2d_rows(const KParams &Q, int &tiles_x, int &tz)
     tz = (Q.nz + tiles_z - 1) / tiles_z;
 }
 
-template <int PR, int MODEL, bool RAGGED, bool CONS>
+template <int PR, int MODEL, int COLS, bool CONS>
 void launch_fused2d_shape(const KParams &Q, const void *src, void *dst, unsigned *flag, hipStream_t s)
 {
     int tiles_x = 0, tz = 0;
     fused2d_rows(Q, tiles_x, tz);
-    const dim3 grid(tiles_x * ((Q.nz + tz - 1) / tz)), block(k2dTX);
-    using S = typename Prec<PR>::S;
-    constexpr int lds = fused_lds_bytes<PR, MODEL, k2dTX, 1, D2Q9Z>();
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)k_fused<PR, MODEL, k2dTX, 1, true, RAGGED, D2Q9, D2Q9Z, CONS>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        (void)hipFuncSetAttribute((const void *)k_fused<PR, MODEL, k2dTX, 1, false, RAGGED, D2Q9, D2Q9Z, CONS>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr_set = true;
-    }
-    if (Q.bc[0] == 0 && Q.bc[2] == 0)
-        hipLaunchKernelGGL((k_fused<PR, MODEL, k2dTX, 1, true, RAGGED, D2Q9, D2Q9Z, CONS>), grid, block, lds, s, Q,
-                           (const S *)src, (S *)dst, flag, tz, tiles_x, 1);
-    else
-        hipLaunchKernelGGL((k_fused<PR, MODEL, k2dTX, 1, false, RAGGED, D2Q9, D2Q9Z, CONS>), grid, block, lds, s, Q,
-                           (const S *)src, (S *)dst, flag, tz, tiles_x, 1);
+    launch_fused_bc<PR, MODEL, k2dTX, 1, COLS, D2Q9, D2Q9Z, CONS>(Q, src, dst, flag, tz, tiles_x, 1, s);
 }
 
 template <int PR, int MODEL>
@@ -645,13 +679,13 @@ void launch_fused2d(const KParams &P, const void *src, void *dst, unsigned *flag
     const KParams Q = as_marching_2d(P);
     if constexpr (kConserveRest<PR> && MODEL == CG) {
         if (P.conserve) {
-            if (Q.nx % k2dTX) launch_fused2d_shape<PR, MODEL, true, true>(Q, src, dst, flag, s);
-            else launch_fused2d_shape<PR, MODEL, false, true>(Q, src, dst, flag, s);
+            if (Q.nx % k2dTX) launch_fused2d_shape<PR, MODEL, kColsRagged, true>(Q, src, dst, flag, s);
+            else launch_fused2d_shape<PR, MODEL, kColsFull, true>(Q, src, dst, flag, s);
             return;
         }
     }
-    if (Q.nx % k2dTX) launch_fused2d_shape<PR, MODEL, true, false>(Q, src, dst, flag, s);
-    else launch_fused2d_shape<PR, MODEL, false, false>(Q, src, dst, flag, s);
+    if (Q.nx % k2dTX) launch_fused2d_shape<PR, MODEL, kColsRagged, false>(Q, src, dst, flag, s);
+    else launch_fused2d_shape<PR, MODEL, kColsFull, false>(Q, src, dst, flag, s);
 }
 
 }  // namespace mclbm

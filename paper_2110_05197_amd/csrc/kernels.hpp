@@ -56,16 +56,128 @@ __device__ __forceinline__ size_t sidx(int k, int i, size_t SW, size_t n)
     else return (size_t)(k * L::Q + i) * SW + n;
 }
 
-// Populations of node n; SW is the array stride KParams::S.
-template <class L, int K, class S, class C, bool NT = false>
-__device__ __forceinline__ void load_node(const S *__restrict__ f, long long SW, long long n,
-                                          C (&g)[K][L::Q])
+// Buffer resources: a base held in scalar registers, a 32-bit byte offset per
+// lane and a 32-bit scalar offset.  A step touches 76 arrays (19 populations,
+// two colours, read and written) at one lane offset or a handful: as 64-bit
+// pointers each access costs a vector add of a base that no longer fits the
+// scalar register file (the one-pass loop spent about 250 of its 1200 vector
+// instructions per node on that, and on moving spilled bases back); as buffer
+// accesses the array is the scalar offset i * stride, 18 scalar registers for
+// all of them, and the lane offset is shared.  Accesses past the resource's
+// size are dropped by the hardware.
+using Rsrc = __amdgpu_buffer_rsrc_t;
+using Words2 = unsigned __attribute__((ext_vector_type(2)));
+
+// A value every lane holds alike, in scalar registers (descriptor fields read
+// from memory are not known to be uniform).
+__device__ __forceinline__ unsigned uniform(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ void *uniform(const void *p)
 {
-    const unsigned o = (unsigned)n;   // N < 2^31: per-lane 32-bit offset, uniform base
+    const uintptr_t v = (uintptr_t)p;
+    const unsigned lo = uniform((unsigned)v), hi = uniform((unsigned)(v >> 32));
+    return (void *)(((uintptr_t)hi << 32) | lo);
+}
+__device__ __forceinline__ Rsrc make_rsrc(const void *p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(uniform(p), 0, (int)uniform(bytes), 0x00020000);
+}
+template <bool NT, class T> __device__ __forceinline__ T buf_ld(Rsrc r, unsigned lane, unsigned scalar)
+{
+    constexpr int aux = NT ? 2 : 0;   // non-temporal
+    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane, scalar, aux));
+    else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane, scalar, aux));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, lane, scalar, aux));
+}
+template <bool NT, class T> __device__ __forceinline__ void buf_st(Rsrc r, unsigned lane, unsigned scalar, T v)
+{
+    constexpr int aux = NT ? 2 : 0;
+    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Words2, v), r, lane, scalar, aux);
+    else if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lane, scalar, aux);
+    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, lane, scalar, aux);
+}
+
+// A node whose near accesses fall outside any buffer (its byte offset is the
+// last word below 4 GB): loads return zero and read nothing.
+constexpr unsigned kNoNode = 0xffffffffu;
+
+// The populations of one buffer.  A word is one population of one node (both
+// colours of it in two-colour FP16 storage, kPairs), a = 0 .. KA-1 the colour
+// of the word.  Near: one resource per colour, for simulations whose Q arrays
+// of one colour span less than 4 GB (KParams::far == 0; FP32 D3Q19 up to about
+// 56 million nodes).  FAR: 64-bit pointers, any size.
+template <class L, int K, class S, bool FAR> struct Pops {
+    using W = std::conditional_t<kPairs<K, S>, Half2, S>;
+    static constexpr int KA = kPairs<K, S> ? 1 : K;
+    Rsrc r[KA];
+    unsigned sb;   // bytes from one population array to the next
+    __device__ __forceinline__ Pops(const void *f, const KParams &P)
+    {
+        sb = uniform((unsigned)P.S) * (unsigned)sizeof(W);
+#pragma unroll
+        for (int a = 0; a < KA; ++a)
+            r[a] = make_rsrc((const char *)f + (size_t)a * L::Q * (size_t)P.S * sizeof(W), (unsigned)L::Q * sb);
+    }
+    template <bool NT = false> __device__ __forceinline__ W load(int a, int i, unsigned n) const
+    {
+        return buf_ld<NT, W>(r[a], n * (unsigned)sizeof(W), (unsigned)i * sb);
+    }
+    template <bool NT = false> __device__ __forceinline__ void store(int a, int i, unsigned n, W v) const
+    {
+        buf_st<NT, W>(r[a], n * (unsigned)sizeof(W), (unsigned)i * sb, v);
+    }
+};
+template <class L, int K, class S> struct Pops<L, K, S, true> {
+    using W = std::conditional_t<kPairs<K, S>, Half2, S>;
+    static constexpr int KA = kPairs<K, S> ? 1 : K;
+    W *f;
+    size_t sw;
+    __device__ __forceinline__ Pops(const void *p, const KParams &P) : f((W *)p), sw((size_t)P.S) {}
+    template <bool NT = false> __device__ __forceinline__ W load(int a, int i, unsigned n) const
+    {
+        return ld<NT>((const W *)&(f + (size_t)(a * L::Q + i) * sw)[n]);
+    }
+    template <bool NT = false> __device__ __forceinline__ void store(int a, int i, unsigned n, W v) const
+    {
+        st<NT>(&(f + (size_t)(a * L::Q + i) * sw)[n], v);
+    }
+};
+
+// Per-node fields of the two-pass step (array a of node n), addressed alike.
+template <class FT, bool FAR> struct Field {
+    Rsrc r;
+    unsigned nb;   // bytes of one array
+    __device__ __forceinline__ Field(const void *f, const KParams &P, int arrays)
+    {
+        nb = uniform((unsigned)P.N) * (unsigned)sizeof(FT);
+        r = make_rsrc(f, (unsigned)arrays * nb);
+    }
+    __device__ __forceinline__ FT load(int a, unsigned n) const
+    {
+        return buf_ld<false, FT>(r, n * (unsigned)sizeof(FT), (unsigned)a * nb);
+    }
+    __device__ __forceinline__ void store(int a, unsigned n, FT v) const
+    {
+        buf_st<false, FT>(r, n * (unsigned)sizeof(FT), (unsigned)a * nb, v);
+    }
+};
+template <class FT> struct Field<FT, true> {
+    FT *f;
+    size_t N;
+    __device__ __forceinline__ Field(const void *p, const KParams &P, int) : f((FT *)p), N((size_t)P.N) {}
+    __device__ __forceinline__ FT load(int a, unsigned n) const { return (f + (size_t)a * N)[n]; }
+    __device__ __forceinline__ void store(int a, unsigned n, FT v) const { (f + (size_t)a * N)[n] = v; }
+};
+// arrays of the stencil field of a model, multirange psi included
+template <int MODEL> constexpr int kFieldArrays = MODEL == CG ? 3 : (MODEL == SC_MP ? 1 : 4);
+
+// Populations of node n.
+template <class L, int K, class S, bool FAR, class C>
+__device__ __forceinline__ void load_node(const Pops<L, K, S, FAR> &f, unsigned n, C (&g)[K][L::Q])
+{
     if constexpr (kPairs<K, S>) {
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
-            const Half2 v = ld<NT>(&(reinterpret_cast<const Half2 *>(f) + (size_t)i * (size_t)SW)[o]);
+            const Half2 v = f.load(0, i, n);
             g[0][i] = (C)v.x;
             g[1][i] = (C)v.y;
         }
@@ -73,59 +185,58 @@ __device__ __forceinline__ void load_node(const S *__restrict__ f, long long SW,
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int i = 0; i < L::Q; ++i) g[k][i] = (C)ld<NT>(&(f + (size_t)(k * L::Q + i) * (size_t)SW)[o]);
+            for (int i = 0; i < L::Q; ++i) g[k][i] = (C)f.load(k, i, n);
     }
+}
+template <class L, int K, class S, class C>
+__device__ __forceinline__ void load_node(const S *__restrict__ f, const KParams &P, long long n, C (&g)[K][L::Q])
+{
+    load_node(Pops<L, K, S, true>(f, P), (unsigned)n, g);   // N < 2^31
 }
 
 // A node's populations held as loaded, for software prefetching: the load is
 // issued early and the conversion to the arithmetic type waits until the
 // values are used (converting on arrival would wait for the load at once).
-template <class L, int K, class S, class C, bool PAIRS = kPairs<K, S>>
-struct RawNode {
-    C v[K][L::Q];
-    __device__ __forceinline__ void load(const S *__restrict__ f, long long SW, long long n)
-    {
-        load_node<L, K>(f, SW, n, v);
-    }
-    __device__ __forceinline__ void get(C (&g)[K][L::Q]) const
-    {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int i = 0; i < L::Q; ++i) g[k][i] = v[k][i];
-    }
-};
 template <class L, int K, class S, class C>
-struct RawNode<L, K, S, C, true> {
-    Half2 v[L::Q];
-    __device__ __forceinline__ void load(const S *__restrict__ f, long long SW, long long n)
+struct RawNode {
+    using W = std::conditional_t<kPairs<K, S>, Half2, S>;
+    static constexpr int KA = kPairs<K, S> ? 1 : K;
+    W v[KA][L::Q];
+    template <bool FAR> __device__ __forceinline__ void load(const Pops<L, K, S, FAR> &f, unsigned n)
     {
 #pragma unroll
-        for (int i = 0; i < L::Q; ++i) v[i] = (reinterpret_cast<const Half2 *>(f) + (size_t)i * (size_t)SW)[(unsigned)n];
+        for (int a = 0; a < KA; ++a)
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) v[a][i] = f.load(a, i, n);
     }
     __device__ __forceinline__ void get(C (&g)[K][L::Q]) const
     {
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
-            g[0][i] = (C)v[i].x;
-            g[1][i] = (C)v[i].y;
+            if constexpr (kPairs<K, S>) {
+                g[0][i] = (C)v[0][i].x;
+                g[1][i] = (C)v[0][i].y;
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k) g[k][i] = (C)v[k][i];
+            }
         }
     }
 };
 
 // Population i of every colour of g stored into slot j of node t.
-template <class L, int K, class S, class C, bool NT>
-__device__ __forceinline__ void store_pop(S *__restrict__ dst, size_t SW, unsigned t, int j, int i,
+template <bool NT, class L, int K, class S, bool FAR, class C>
+__device__ __forceinline__ void store_pop(const Pops<L, K, S, FAR> &dst, unsigned t, int j, int i,
                                           const C (&g)[K][L::Q])
 {
     if constexpr (kPairs<K, S>) {
         Half2 v;
         v.x = (S)g[0][i];
         v.y = (S)g[1][i];
-        st<NT>(&(reinterpret_cast<Half2 *>(dst) + (size_t)j * SW)[t], v);
+        dst.template store<NT>(0, j, t, v);
     } else {
 #pragma unroll
-        for (int k = 0; k < K; ++k) st<NT>(&(dst + (size_t)(k * L::Q + j) * SW)[t], (S)g[k][i]);
+        for (int k = 0; k < K; ++k) dst.template store<NT>(k, j, t, (S)g[k][i]);
     }
 }
 
@@ -133,41 +244,49 @@ __device__ __forceinline__ void store_pop(S *__restrict__ dst, size_t SW, unsign
 // (periodic wrap), bounces back into the opposite direction at the same node
 // when x + c_i is behind a wall, and leaves when it is behind an outflow face
 // only (the outflow completion supplies the entering populations afterwards).
+// The lattice L places the neighbours; G holds the populations' types.
 // NTA: store the populations with c_x = 0 (whose targets keep the row's cache
 // line alignment) with the non-temporal hint.
-template <class L, int K, class S, class C, bool NTA = false>
-__device__ __forceinline__ void push_store_general(const KParams &P, S *__restrict__ dst, int x, int y, int z,
-                                                   long long n, const C (&g)[K][L::Q])
+template <class L, bool NTA, class G, int K, class S, bool FAR, class C>
+__device__ __forceinline__ void push_store_general(const KParams &P, const Pops<G, K, S, FAR> &dst, int x, int y,
+                                                   int z, unsigned n, const C (&g)[K][G::Q])
 {
-    const size_t SW = (size_t)P.S;
+    // per axis and step -1, 0, +1: the target's share of the node index and
+    // whether it lies behind a wall (1) or an outflow face (2)
+    unsigned ox[3], oy[3], oz[3];
+    int kx[3], ky[3], kz[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        kx[d] = ky[d] = kz[d] = 0;
+        ox[d] = (unsigned)push_coord(x + d - 1, P.nx, P.bc[0], kx[d]);
+        oy[d] = (unsigned)push_coord(y + d - 1, P.ny, P.bc[1], ky[d]) * (unsigned)P.nx;
+        oz[d] = (unsigned)push_coord(z + d - 1, P.nz, P.bc[2], kz[d]) * (unsigned)(P.nx * P.ny);
+    }
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) {
-        int kind = 0;
-        const int tx = push_coord(x + L::cx[i], P.nx, P.bc[0], kind);
-        const int ty = push_coord(y + L::cy[i], P.ny, P.bc[1], kind);
-        const int tz = push_coord(z + L::cz[i], P.nz, P.bc[2], kind);
+        const int kind = kx[1 + L::cx[i]] | ky[1 + L::cy[i]] | kz[1 + L::cz[i]];
         const int o = i == 0 ? 0 : ((i & 1) ? i + 1 : i - 1);
         if (kind & 1) {
-            store_pop<L, K, S, C, false>(dst, SW, (unsigned)n, o, i, g);
+            store_pop<false>(dst, n, o, i, g);
         } else if (kind == 0) {
-            const unsigned t = (unsigned)tx + (unsigned)P.nx * ((unsigned)ty + (unsigned)P.ny * (unsigned)tz);
-            if (NTA && L::cx[i] == 0) store_pop<L, K, S, C, true>(dst, SW, t, i, i, g);
-            else store_pop<L, K, S, C, false>(dst, SW, t, i, i, g);
+            const unsigned t = ox[1 + L::cx[i]] + oy[1 + L::cy[i]] + oz[1 + L::cz[i]];
+            if (NTA && L::cx[i] == 0) store_pop<true>(dst, t, i, i, g);
+            else store_pop<false>(dst, t, i, i, g);
         }
     }
 }
 
 // All-periodic push: the target of direction i is n + c_i . (1, nx, nx ny)
 // with a wrap correction on the faces, selected at compile time per i.
-template <class L, int K, class S, class C, bool NTA = false>
-__device__ __forceinline__ void push_store_periodic(const KParams &P, S *__restrict__ dst, int x, int y, int z,
-                                                    long long n, const C (&g)[K][L::Q])
+template <class L, bool NTA, class G, int K, class S, bool FAR, class C>
+__device__ __forceinline__ void push_store_periodic(const KParams &P, const Pops<G, K, S, FAR> &dst, int x, int y,
+                                                    int z, unsigned n, const C (&g)[K][G::Q])
 {
-    const size_t N = (size_t)P.N, SW = (size_t)P.S;
+    const int N = (int)P.N;
     const int nx = P.nx, sxy = P.nx * P.ny;
     const int dxp = x == P.nx - 1 ? 1 - nx : 1, dxm = x == 0 ? nx - 1 : -1;
     const int dyp = y == P.ny - 1 ? nx - sxy : nx, dym = y == 0 ? sxy - nx : -nx;
-    const int dzp = z == P.nz - 1 ? sxy - (int)N : sxy, dzm = z == 0 ? (int)N - sxy : -sxy;
+    const int dzp = z == P.nz - 1 ? sxy - N : sxy, dzm = z == 0 ? N - sxy : -sxy;
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) {
         int d = 0;
@@ -175,17 +294,42 @@ __device__ __forceinline__ void push_store_periodic(const KParams &P, S *__restr
         if (L::cy[i]) d += L::cy[i] > 0 ? dyp : dym;
         if (L::cz[i]) d += L::cz[i] > 0 ? dzp : dzm;
         const unsigned t = (unsigned)((int)n + d);
-        if (NTA && L::cx[i] == 0) store_pop<L, K, S, C, true>(dst, SW, t, i, i, g);
-        else store_pop<L, K, S, C, false>(dst, SW, t, i, i, g);
+        if (NTA && L::cx[i] == 0) store_pop<true>(dst, t, i, i, g);
+        else store_pop<false>(dst, t, i, i, g);
     }
 }
 
-template <class L, int K, class S, class C>
-__device__ __forceinline__ void push_store(const KParams &P, S *__restrict__ dst, int x, int y, int z,
-                                           long long n, const C (&g)[K][L::Q])
+template <class L, bool PERIODIC, class G, int K, class S, bool FAR, class C>
+__device__ __forceinline__ void push_store(const KParams &P, const Pops<G, K, S, FAR> &dst, int x, int y, int z,
+                                           unsigned n, const C (&g)[K][G::Q])
 {
-    if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0) push_store_periodic<L, K>(P, dst, x, y, z, n, g);
-    else push_store_general<L, K>(P, dst, x, y, z, n, g);
+    if (PERIODIC || (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0)) push_store_periodic<L, false>(P, dst, x, y, z, n, g);
+    else push_store_general<L, false>(P, dst, x, y, z, n, g);
+}
+
+// Coordinates of node n.
+__device__ __forceinline__ void node_coords(const KParams &P, unsigned n, int &x, int &y, int &z)
+{
+    const unsigned row = n / (unsigned)P.nx;
+    x = (int)(n - row * (unsigned)P.nx);
+    z = (int)(row / (unsigned)P.ny);
+    y = (int)(row - (unsigned)z * (unsigned)P.ny);
+}
+
+// Node indices of the stencil neighbours of (x, y, z): per axis the wrapped or
+// clamped coordinates of the three planes, then one sum per direction.
+template <class L>
+__device__ __forceinline__ void stencil_nodes(const KParams &P, int x, int y, int z, unsigned (&nb)[L::Q])
+{
+    unsigned ox[3], oy[3], oz[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        ox[d] = (unsigned)stencil_coord(x + d - 1, P.nx, P.bc[0]);
+        oy[d] = (unsigned)stencil_coord(y + d - 1, P.ny, P.bc[1]) * (unsigned)P.nx;
+        oz[d] = (unsigned)stencil_coord(z + d - 1, P.nz, P.bc[2]) * (unsigned)(P.nx * P.ny);
+    }
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i) nb[i] = ox[1 + L::cx[i]] + oy[1 + L::cy[i]] + oz[1 + L::cz[i]];
 }
 
 // ---------------------------------------------------------------------------
@@ -193,32 +337,32 @@ __device__ __forceinline__ void push_store(const KParams &P, S *__restrict__ dst
 //   CG: drho_R, drho_B, rho^N;  SC_MP: psi(rho);  SC_MC: drho_R, drho_B.
 // Returns whether the node is diverged (non-finite or rho <= 0).
 // ---------------------------------------------------------------------------
-template <class L, int PR, int MODEL>
-__device__ __forceinline__ bool density_body(const KParams &P, const typename Prec<PR>::S *__restrict__ f,
-                                             typename Prec<PR>::F *__restrict__ field, long long n)
+template <class L, int PR, int MODEL, bool FAR>
+__device__ __forceinline__ bool density_body(const KParams &P, const void *f, void *field, unsigned n)
 {
     using C = typename Prec<PR>::C;
     using M = typename Prec<PR>::M;
     using FT = typename Prec<PR>::F;
     constexpr int K = NComp<MODEL>::n;
+    const Field<FT, FAR> fv(field, P, kFieldArrays<MODEL>);
     C g[K][L::Q];
-    load_node<L, K>(f, P.S, n, g);
+    load_node(Pops<L, K, typename Prec<PR>::S, FAR>(f, P), n, g);
     M dr[2], j[3];
     node_moments<L, K>(g, dr, j);
     const HP<C, M> H = make_hp<C, M>(P);
     const M r = H.rho0[0] + dr[0] + (K == 2 ? H.rho0[1] + dr[1] : M(0));
     if constexpr (MODEL == CG) {
-        field[n] = (FT)dr[0];
-        field[P.N + n] = (FT)dr[1];
-        field[2 * P.N + n] = (FT)colour_field(H, dr[0], dr[1]);
+        fv.store(0, n, (FT)dr[0]);
+        fv.store(1, n, (FT)dr[1]);
+        fv.store(2, n, (FT)colour_field(H, dr[0], dr[1]));
     } else if constexpr (MODEL == SC_MP) {
-        field[n] = (FT)pseudo_potential(H, H.rho0[0] + dr[0]);
+        fv.store(0, n, (FT)pseudo_potential(H, H.rho0[0] + dr[0]));
     } else {
-        field[n] = (FT)dr[0];
-        field[P.N + n] = (FT)dr[1];
+        fv.store(0, n, (FT)dr[0]);
+        fv.store(1, n, (FT)dr[1]);
         if (P.multirange) {
-            field[2 * P.N + n] = (FT)pseudo_potential(H, H.rho0[0] + dr[0]);
-            field[3 * P.N + n] = (FT)pseudo_potential(H, H.rho0[1] + dr[1]);
+            fv.store(2, n, (FT)pseudo_potential(H, H.rho0[0] + dr[0]));
+            fv.store(3, n, (FT)pseudo_potential(H, H.rho0[1] + dr[1]));
         }
     }
     return node_bad(r, j[0] + j[1] + j[2]);
@@ -332,45 +476,47 @@ __device__ __forceinline__ void add_multirange(const KParams &P, const MrStaged<
     multirange_forces<T>(P, s.R, s.B, ox, oy, oz, FR, FB);
 }
 
-// Gradient field of rho^N (repulsion variant): 3 sum w rho^N(x + c) c.
-template <class L, int PR>
-__device__ __forceinline__ void gradN_body(const KParams &P, const typename Prec<PR>::F *__restrict__ field,
-                                           typename Prec<PR>::F *__restrict__ gfield, long long n)
+// Unit normal of the interface at a node (repulsion variant, Eqs. normal1,
+// normal2): grad rho^N / |grad rho^N| with grad rho^N = 3 sum w rho^N(x + c) c,
+// zero where |grad rho^N| <= g_min.  A node's normal is read by itself and its
+// 18 neighbours, so it is normalised here, once, rather than by every reader.
+template <class L, int PR, bool FAR>
+__device__ __forceinline__ void normal_body(const KParams &P, const void *field, void *nfield, unsigned n)
 {
     using C = typename Prec<PR>::C;
-    const int x = (int)(n % P.nx), y = (int)((n / P.nx) % P.ny), z = (int)(n / ((long long)P.nx * P.ny));
+    using FT = typename Prec<PR>::F;
+    const Field<FT, FAR> fv(field, P, kFieldArrays<CG>), nv(nfield, P, 3);
+    int x, y, z;
+    node_coords(P, n, x, y, z);
+    unsigned nb[L::Q];
+    stencil_nodes<L>(P, x, y, z, nb);
     C v[L::Q];
     v[0] = C(0);
 #pragma unroll
-    for (int i = 1; i < L::Q; ++i) v[i] = (C)field[2 * P.N + stencil_node<L>(P, x, y, z, i)];
+    for (int i = 1; i < L::Q; ++i) v[i] = (C)fv.load(2, nb[i]);
     C s[3];
     stencil_sum<L>(v, s);
+    C g[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) gfield[d * P.N + n] = (typename Prec<PR>::F)(C(3) * s[d]);
+    for (int d = 0; d < 3; ++d) g[d] = C(3) * s[d];
+    const C gn = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
+    const C k = gn > (C)P.g_min ? C(1) / gn : C(0);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) nv.store(d, n, (FT)(g[d] * k));
 }
 
-// Repulsion force at (x, y, z) (Eq. repForce; psi_rep = (1 - |rho^N|)^chi;
-// applied outward from the extremum of rho^N, as section 2.3 describes).
-template <class L, class C, class FT>
-__device__ __forceinline__ void repulsion_force(const KParams &P, const FT *__restrict__ field,
-                                                const FT *__restrict__ gfield, int x, int y, int z,
-                                                long long n, C (&F)[3])
+// Repulsion force at node n (Eq. repForce; psi_rep = (1 - |rho^N|)^chi;
+// applied outward from the extremum of rho^N, as section 2.3 describes), from
+// the normals of the pass before; nb: its stencil neighbours.
+template <class L, class C, class FT, bool FAR>
+__device__ __forceinline__ void repulsion_force(const KParams &P, const Field<FT, FAR> &fv, const Field<FT, FAR> &nf,
+                                                const unsigned (&nb)[L::Q], unsigned n, C (&F)[3])
 {
-    const long long N = P.N;
-    C nv[3] = {(C)gfield[n], (C)gfield[N + n], (C)gfield[2 * N + n]};
-    {
-        const C gn = sqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
-        const C s = gn > (C)P.g_min ? C(1) / gn : C(0);
-        nv[0] *= s; nv[1] *= s; nv[2] *= s;
-    }
+    const C nv[3] = {(C)nf.load(0, n), (C)nf.load(1, n), (C)nf.load(2, n)};
     C acc[3] = {C(0), C(0), C(0)};
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
-        const long long m = stencil_node<L>(P, x, y, z, i);
-        C np[3] = {(C)gfield[m], (C)gfield[N + m], (C)gfield[2 * N + m]};
-        const C gp = sqrt(np[0] * np[0] + np[1] * np[1] + np[2] * np[2]);
-        const C s = gp > (C)P.g_min ? C(1) / gp : C(0);
-        np[0] *= s; np[1] *= s; np[2] *= s;
+        const C np[3] = {(C)nf.load(0, nb[i]), (C)nf.load(1, nb[i]), (C)nf.load(2, nb[i])};
         const C nc = cdot<L>(i, nv), npc = cdot<L>(i, np);
         if (-(nc * npc) > C(0)) {
             const C il = (C)L::inv_len[L::grp[i]];
@@ -380,7 +526,7 @@ __device__ __forceinline__ void repulsion_force(const KParams &P, const FT *__re
     }
     // outward, away from the extremum of rho^N between the interfaces: minus
     // the sum above, which points toward it
-    const C rn = (C)field[2 * N + n];
+    const C rn = (C)fv.load(2, n);
     const C psi = pow(C(1) - fabs(rn), (C)P.chi);
 #pragma unroll
     for (int d = 0; d < 3; ++d) F[d] = -(C)P.Pi * psi * acc[d];
@@ -389,37 +535,37 @@ __device__ __forceinline__ void repulsion_force(const KParams &P, const FT *__re
 // ---------------------------------------------------------------------------
 // Collide + push-stream of one node, reading stencil inputs from the field.
 // REP: with the model's extended force (CG repulsion, SC_MC multirange).
+// PERIODIC: all faces are (otherwise the push looks).
 // ---------------------------------------------------------------------------
 // MR: where the multirange forces read psi (MrGlobal: the field; MrStaged: a
 // box in LDS).
-template <class L, int PR, int MODEL, bool REP, class MR = MrGlobal>
-__device__ __forceinline__ void collide_body(const KParams &P, const typename Prec<PR>::S *__restrict__ src,
-                                             typename Prec<PR>::S *__restrict__ dst,
-                                             const typename Prec<PR>::F *__restrict__ field,
-                                             const typename Prec<PR>::F *__restrict__ gfield, long long n,
-                                             const MR &mr = MR{})
+template <class L, int PR, int MODEL, bool REP, bool FAR, bool PERIODIC = false, class MR = MrGlobal>
+__device__ __forceinline__ void collide_body(const KParams &P, const void *src, void *dst, const void *field,
+                                             const void *nfield, unsigned n, const MR &mr = MR{})
 {
     using C = typename Prec<PR>::C;
     using M = typename Prec<PR>::M;
+    using S = typename Prec<PR>::S;
+    using FT = typename Prec<PR>::F;
     constexpr int K = NComp<MODEL>::n;
-    const long long N = P.N;
-    const int x = (int)(n % P.nx), y = (int)((n / P.nx) % P.ny), z = (int)(n / ((long long)P.nx * P.ny));
+    int x, y, z;
+    node_coords(P, n, x, y, z);
     const HP<C, M> H = make_hp<C, M>(P);
+    const Field<FT, FAR> fv(field, P, kFieldArrays<MODEL>);
     C g[K][L::Q];
-    load_node<L, K>(src, P.S, n, g);
+    load_node(Pops<L, K, S, FAR>(src, P), n, g);
     M dr[2], j[3];
     node_moments<L, K>(g, dr, j);
-    long long nb[L::Q];
-#pragma unroll
-    for (int i = 1; i < L::Q; ++i) nb[i] = stencil_node<L>(P, x, y, z, i);
+    unsigned nb[L::Q];
+    stencil_nodes<L>(P, x, y, z, nb);
     if constexpr (MODEL == CG) {
         C vR[L::Q], vB[L::Q], vN[L::Q];
         vR[0] = vB[0] = vN[0] = C(0);
 #pragma unroll
         for (int i = 1; i < L::Q; ++i) {
-            vR[i] = (C)field[nb[i]];
-            vB[i] = (C)field[N + nb[i]];
-            vN[i] = (C)field[2 * N + nb[i]];
+            vR[i] = (C)fv.load(0, nb[i]);
+            vB[i] = (C)fv.load(1, nb[i]);
+            vN[i] = (C)fv.load(2, nb[i]);
         }
         C gR[3], gB[3], gN[3];
         stencil_sum<L>(vR, gR);
@@ -428,16 +574,16 @@ __device__ __forceinline__ void collide_body(const KParams &P, const typename Pr
 #pragma unroll
         for (int d = 0; d < 3; ++d) { gR[d] *= C(3); gB[d] *= C(3); gN[d] *= C(3); }
         C F[3] = {C(0), C(0), C(0)};
-        if constexpr (REP) repulsion_force<L>(P, field, gfield, x, y, z, n, F);
+        if constexpr (REP) repulsion_force<L>(P, fv, Field<FT, FAR>(nfield, P, 3), nb, n, F);
         cg_collide<L, C, M, REP, kConsShared<PR>>(H, g, dr, j, gR, gB, gN, F);
     } else if constexpr (MODEL == SC_MP) {
         C v[L::Q];
         v[0] = C(0);
 #pragma unroll
-        for (int i = 1; i < L::Q; ++i) v[i] = (C)field[nb[i]];
+        for (int i = 1; i < L::Q; ++i) v[i] = (C)fv.load(0, nb[i]);
         C s[3];
         stencil_sum<L>(v, s);
-        const C psi = (C)field[n];
+        const C psi = (C)fv.load(0, n);
         const M rho = H.rho0[0] + dr[0];
         const M irho = rcp(rho);
         C F[3], u[3];
@@ -452,8 +598,8 @@ __device__ __forceinline__ void collide_body(const KParams &P, const typename Pr
         vR[0] = vB[0] = C(0);
 #pragma unroll
         for (int i = 1; i < L::Q; ++i) {
-            vR[i] = (C)field[nb[i]];
-            vB[i] = (C)field[N + nb[i]];
+            vR[i] = (C)fv.load(0, nb[i]);
+            vB[i] = (C)fv.load(1, nb[i]);
         }
         C sR[3], sB[3];
         stencil_sum<L>(vR, sR);
@@ -467,7 +613,7 @@ __device__ __forceinline__ void collide_body(const KParams &P, const typename Pr
             FB[d] = -H.xpref * (C)rB * sR[d];
         }
         if constexpr (REP) {   // extended force: multirange
-            if constexpr (std::is_same_v<MR, MrGlobal>) add_multirange<C>(P, field, x, y, z, FR, FB);
+            if constexpr (std::is_same_v<MR, MrGlobal>) add_multirange<C>(P, (const FT *)field, x, y, z, FR, FB);
             else add_multirange<C>(P, mr, FR, FB);
         }
 #pragma unroll
@@ -475,7 +621,7 @@ __device__ __forceinline__ void collide_body(const KParams &P, const typename Pr
         sc_collide_component<L, C, M>(g[0], H.om[0], dr[0], rR, u, FR, H.rho0[0], H.corrM[0], H.shiftM[0]);
         sc_collide_component<L, C, M>(g[1], H.om[1], dr[1], rB, u, FB, H.rho0[1], H.corrM[1], H.shiftM[1]);
     }
-    push_store<L, K>(P, dst, x, y, z, n, g);
+    push_store<L, PERIODIC>(P, Pops<L, K, S, FAR>(dst, P), x, y, z, n, g);
 }
 
 // Outflow completion for one face node: populations that would come from
@@ -590,7 +736,7 @@ __device__ __forceinline__ bool node_state64(const KParams &P, const typename Pr
     constexpr int K = NComp<MODEL>::n;
     const long long N = P.N;
     double g[K][L::Q];
-    load_node<L, K>(f, P.S, n, g);
+    load_node<L, K>(f, P, n, g);
     double dr[2];
     node_moments<L, K>(g, dr, j);
     rR = P.rho0[0] + dr[0];

@@ -18,32 +18,31 @@ __device__ __forceinline__ void flag_if_bad(unsigned *flag, bool bad)
 }
 
 // ----------------------------- solo kernels --------------------------------
-template <class L, int PR, int MODEL>
-__global__ __launch_bounds__(kBlock) void k_density(KParams P, const typename Prec<PR>::S *__restrict__ f,
-                                                    typename Prec<PR>::F *__restrict__ field, unsigned *flag)
+// FAR: 64-bit addressing (KParams::far); else buffer resources.
+__device__ __forceinline__ unsigned block_node(unsigned block) { return block * (unsigned)kBlock + threadIdx.x; }
+
+template <class L, int PR, int MODEL, bool FAR>
+__global__ __launch_bounds__(kBlock) void k_density(KParams P, const void *f, void *field, unsigned *flag)
 {
-    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned n = block_node(blockIdx.x);
     bool bad = false;
-    if (n < P.N) bad = density_body<L, PR, MODEL>(P, f, field, n);
+    if (n < (unsigned)P.N) bad = density_body<L, PR, MODEL, FAR>(P, f, field, n);
     flag_if_bad(flag, bad);
 }
 
-template <class L, int PR>
-__global__ __launch_bounds__(kBlock) void k_gradN(KParams P, const typename Prec<PR>::F *__restrict__ field,
-                                                  typename Prec<PR>::F *__restrict__ gfield)
+template <class L, int PR, bool FAR>
+__global__ __launch_bounds__(kBlock) void k_normals(KParams P, const void *field, void *nfield)
 {
-    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (n < P.N) gradN_body<L, PR>(P, field, gfield, n);
+    const unsigned n = block_node(blockIdx.x);
+    if (n < (unsigned)P.N) normal_body<L, PR, FAR>(P, field, nfield, n);
 }
 
-template <class L, int PR, int MODEL, bool REP>
-__global__ __launch_bounds__(kBlock) void k_collide(KParams P, const typename Prec<PR>::S *__restrict__ src,
-                                                    typename Prec<PR>::S *__restrict__ dst,
-                                                    const typename Prec<PR>::F *__restrict__ field,
-                                                    const typename Prec<PR>::F *__restrict__ gfield)
+template <class L, int PR, int MODEL, bool REP, bool FAR, bool PERIODIC>
+__global__ __launch_bounds__(kBlock) void k_collide(KParams P, const void *src, void *dst, const void *field,
+                                                    const void *nfield)
 {
-    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (n < P.N) collide_body<L, PR, MODEL, REP>(P, src, dst, field, gfield, n);
+    const unsigned n = block_node(blockIdx.x);
+    if (n < (unsigned)P.N) collide_body<L, PR, MODEL, REP, FAR, PERIODIC>(P, src, dst, field, nfield, n);
 }
 
 // Stages two fields (a, b) of a box in LDS: columns x0 - RCH .. x0 - RCH +
@@ -98,12 +97,12 @@ template <int PR> constexpr int kMrWaves = PR == 1 ? 4 : PR == 0 ? 2 : 3;
 // tile, z), first stages in LDS psi_R and psi_B of the tile and two nodes
 // around it, then collides its nodes with the multirange sums reading that
 // box (the one-node stencil of the cross force reads the field).
-template <int PR>
+template <int PR, bool FAR, bool PERIODIC>
 __global__ __launch_bounds__(kMrTX *kMrTY) __attribute__((amdgpu_waves_per_eu(kMrWaves<PR>)))
-void k_collide_mr(KParams P, const typename Prec<PR>::S *__restrict__ src, typename Prec<PR>::S *__restrict__ dst,
-                  const typename Prec<PR>::F *__restrict__ field)
+void k_collide_mr(KParams P, const void *src, void *dst, const void *fieldp)
 {
     using FT = typename Prec<PR>::F;
+    const FT *field = (const FT *)fieldp;
     __shared__ FT psiR[kMrBox], psiB[kMrBox];
     const int tiles_x = (P.nx + kMrTX - 1) / kMrTX, tiles_y = (P.ny + kMrTY - 1) / kMrTY;
     const int b = (int)blockIdx.x;
@@ -113,8 +112,9 @@ void k_collide_mr(KParams P, const typename Prec<PR>::S *__restrict__ src, typen
     const int tx = (int)threadIdx.x % kMrTX, ty = (int)threadIdx.x / kMrTX;
     const int x = x0 + tx, y = y0 + ty;
     if (x >= P.nx || y >= P.ny) return;
-    const long long n = (long long)x + (long long)P.nx * ((long long)y + (long long)P.ny * z);
-    collide_body<D3Q19, PR, SC_MC, true>(P, src, dst, field, nullptr, n, MrStaged<FT>{psiR, psiB, tx, ty});
+    const unsigned n = (unsigned)x + (unsigned)P.nx * ((unsigned)y + (unsigned)P.ny * (unsigned)z);
+    collide_body<D3Q19, PR, SC_MC, true, FAR, PERIODIC>(P, src, dst, field, nullptr, n,
+                                                        MrStaged<FT>{psiR, psiB, tx, ty});
 }
 
 inline long long mr_blocks(const KParams &P)
@@ -204,7 +204,7 @@ struct SimDesc {
     KParams P;
     void *f[2];
     void *field;
-    void *gfield;
+    void *nfield;
     unsigned *flag;
     long long block0, nblocks;     // node-parallel grid slice
     long long oblock0, onblocks;   // outflow-face grid slice
@@ -236,64 +236,46 @@ __device__ __forceinline__ int find_sim(const SimDesc *D, int n, long long b, bo
     return lo;
 }
 
-template <class L, int PR, int MODEL>
+// Each two-pass batch kernel comes near and FAR; a block whose simulation is
+// of the other kind returns at once.
+template <class L, int PR, int MODEL, bool FAR>
 __global__ __launch_bounds__(kBlock) void kb_density(SimDesc *D, int nsims)
 {
     const int s = find_sim(D, nsims, blockIdx.x, false);
     const SimDesc &d = D[s];
-    if (d.state != 0) return;
-    const long long n = (blockIdx.x - d.block0) * kBlock + threadIdx.x;
+    if (d.state != 0 || (d.P.far != 0) != FAR) return;
+    const unsigned n = block_node(blockIdx.x - (unsigned)d.block0);
     bool bad = false;
-    if (n < d.P.N)
-        bad = density_body<L, PR, MODEL>(d.P, global_ptr<const typename Prec<PR>::S>(d.f[d.cur]),
-                                         global_ptr<typename Prec<PR>::F>(d.field), n);
+    if (n < (unsigned)d.P.N) bad = density_body<L, PR, MODEL, FAR>(d.P, global_ptr<char>(d.f[d.cur]), global_ptr<char>(d.field), n);
     flag_if_bad(global_ptr<unsigned>(d.flag), bad);
 }
 
-template <class L, int PR, int MODEL, bool REP>
+template <class L, int PR, int MODEL, bool REP, bool FAR>
 __device__ __forceinline__ void kb_collide_body(SimDesc *D, int nsims)
 {
     const int s = find_sim(D, nsims, blockIdx.x, false);
     const SimDesc &d = D[s];
-    if (d.state != 0) return;
-    const long long n = (blockIdx.x - d.block0) * kBlock + threadIdx.x;
-    if (n < d.P.N)
-        collide_body<L, PR, MODEL, REP>(d.P, global_ptr<const typename Prec<PR>::S>(d.f[d.cur]),
-                                        global_ptr<typename Prec<PR>::S>(d.f[d.cur ^ 1]),
-                                        global_ptr<const typename Prec<PR>::F>(d.field),
-                                        global_ptr<const typename Prec<PR>::F>(d.gfield), n);
+    if (d.state != 0 || (d.P.far != 0) != FAR) return;
+    const unsigned n = block_node(blockIdx.x - (unsigned)d.block0);
+    if (n < (unsigned)d.P.N)
+        collide_body<L, PR, MODEL, REP, FAR>(d.P, global_ptr<char>(d.f[d.cur]), global_ptr<char>(d.f[d.cur ^ 1]),
+                                             global_ptr<char>(d.field), global_ptr<char>(d.nfield), n);
 }
 
-template <class L, int PR, int MODEL, bool REP>
+template <class L, int PR, int MODEL, bool REP, bool FAR>
 __global__ __launch_bounds__(kBlock) void kb_collide(SimDesc *D, int nsims)
 {
-    kb_collide_body<L, PR, MODEL, REP>(D, nsims);
+    kb_collide_body<L, PR, MODEL, REP, FAR>(D, nsims);
 }
 
-// The same kernel compiled for three waves per SIMD, for the D3Q19 mixed
-// colour-gradient collide: left to itself the compiler gives it 172
-// registers a lane (two waves); at three it holds 168 with no spill, and a
-// batch of eight 80^3 two-pass lattices stepped in 0.450 instead of 0.483 ms.
-// (Caps that make the other collides spill slowed them, up to twofold.)
-template <class L, int PR, int MODEL, bool REP>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
-void kb_collide_w3(SimDesc *D, int nsims)
-{
-    kb_collide_body<L, PR, MODEL, REP>(D, nsims);
-}
-template <class L, int PR, int MODEL, bool REP>
-constexpr bool kb_collide_three_waves = L::Q == 19 && PR == 2 && MODEL == CG && !REP;
-
-template <class L, int PR>
-__global__ __launch_bounds__(kBlock) void kb_gradN(SimDesc *D, int nsims)
+template <class L, int PR, bool FAR>
+__global__ __launch_bounds__(kBlock) void kb_normals(SimDesc *D, int nsims)
 {
     const int s = find_sim(D, nsims, blockIdx.x, false);
     const SimDesc &d = D[s];
-    if (d.state != 0) return;
-    const long long n = (blockIdx.x - d.block0) * kBlock + threadIdx.x;
-    if (n < d.P.N)
-        gradN_body<L, PR>(d.P, global_ptr<const typename Prec<PR>::F>(d.field),
-                          global_ptr<typename Prec<PR>::F>(d.gfield), n);
+    if (d.state != 0 || (d.P.far != 0) != FAR) return;
+    const unsigned n = block_node(blockIdx.x - (unsigned)d.block0);
+    if (n < (unsigned)d.P.N) normal_body<L, PR, FAR>(d.P, global_ptr<char>(d.field), global_ptr<char>(d.nfield), n);
 }
 
 template <class L, int PR, int MODEL>

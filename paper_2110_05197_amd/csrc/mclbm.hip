@@ -69,7 +69,7 @@ size_t field_size(int prec) { return prec == MCLBM_FP64 ? 8 : 4; }
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct Layout {
-    size_t fbytes, field_off, gfield_off, total;
+    size_t fbytes, field_off, nfield_off, total;
 };
 
 // Population arrays: the word one array element holds (two-colour FP16
@@ -112,9 +112,9 @@ Layout layout_of(const mclbm_params &p)
     Layout L;
     L.fbytes = align256(pop_arrays(p) * (size_t)pop_stride(p) * pop_word(p));
     L.field_off = 2 * L.fbytes;
-    L.gfield_off = L.field_off + align256((size_t)nfield_of(p) * N * field_size(p.precision));
+    L.nfield_off = L.field_off + align256((size_t)nfield_of(p) * N * field_size(p.precision));
     const bool rep = p.model == MCLBM_CG && p.Pi != 0.0;
-    L.total = L.gfield_off + (rep ? align256(3 * N * field_size(p.precision)) : 0);
+    L.total = L.nfield_off + (rep ? align256(3 * N * field_size(p.precision)) : 0);
     return L;
 }
 
@@ -239,6 +239,20 @@ KParams make_kparams(const mclbm_params &p)
     for (int d = 0; d < 3; ++d) K.bc[d] = p.bc[d];
     K.N = (long long)p.nx * p.ny * p.nz;
     K.S = pop_stride(p);
+    // the buffer resources of the step kernels hold byte offsets in 32 bits
+    K.far = (unsigned long long)lattice_Q(p.lattice) * (unsigned long long)K.S * pop_word(p) >= (1ull << 32) ? 1 : 0;
+    // D3Q19 rows that do not start on a cache line each: the one-pass kernels'
+    // lines are then shared by the rows above and below, and tightly issued
+    // buffer loads miss what the pointer loads, spaced by their address
+    // arithmetic, find in L2.  FP32, pointers and buffers (ms per step):
+    // 234 x 80 x 119 colour gradient 0.218 and 0.230, 201 x 160 x 170 0.588
+    // and 0.602; on line-aligned rows 160^3 0.357 and 0.331, 192^3 with walls
+    // 0.68 and 0.616.  FP16 storage gains either way (250 x 120 x 101: 0.166
+    // and 0.155), and so do boxes of one column (27 x 32 x 230 FP32: 0.0304
+    // and 0.0275).
+    K.far_rows = K.far
+                 || (p.lattice == MCLBM_D3Q19 && p.precision != MCLBM_FP16 && p.nx > 64
+                     && (unsigned long long)p.nx * pop_word(p) % 128 != 0) ? 1 : 0;
     K.enhanced = p.enhanced_eq ? 1 : 0;
     K.conserve = p.model == MCLBM_CG && (p.precision == MCLBM_FP32 || p.precision == MCLBM_MIXED)
                  && p.conserve_mass ? 1 : 0;
@@ -514,7 +528,7 @@ struct mclbm_sim {
     char *base;
     void *f[2];
     void *field;
-    void *gfield;
+    void *nfield;
     int cur;
     int64_t step;
     hipStream_t stream;
@@ -544,7 +558,8 @@ struct mclbm_batch {
         const Ops *ops;
         int first, count;
         long long blocks, fblocks, oblocks;
-        int fused_kinds;   // fused_kind() bits of its one-pass sims
+        int two_pass_kinds;   // kTwoPassNear / kTwoPassFar of its two-pass sims
+        int fused_kinds;      // fused_kind() bits of its one-pass sims
         bool any_outflow;
     };
     std::vector<Group> groups;
@@ -689,7 +704,7 @@ mclbm_status mclbm_create(const mclbm_params *p, void *d_state, size_t bytes, vo
     sim->f[0] = sim->base;
     sim->f[1] = sim->base + lay.fbytes;
     sim->field = sim->base + lay.field_off;
-    sim->gfield = sim->base + lay.gfield_off;
+    sim->nfield = sim->base + lay.nfield_off;
     sim->cur = 0;
     sim->step = 0;
     sim->stream = (hipStream_t)stream;
@@ -800,7 +815,7 @@ mclbm_status mclbm_step(mclbm_sim *sim, int64_t nsteps, int64_t check_every, int
     if (nsteps < 0 || check_every < 0) return fail(MCLBM_EINVAL, "negative step count");
     int64_t done = 0;
     for (int64_t t = 0; t < nsteps; ++t) {
-        sim->ops->step(sim->kp, sim->f[sim->cur], sim->f[sim->cur ^ 1], sim->field, sim->gfield, sim->d_flag,
+        sim->ops->step(sim->kp, sim->f[sim->cur], sim->f[sim->cur ^ 1], sim->field, sim->nfield, sim->d_flag,
                        sim->fused, sim->stream);
         sim->cur ^= 1;
         ++sim->step;
@@ -991,6 +1006,7 @@ mclbm_status mclbm_batch_create(mclbm_sim *const *sims, int32_t n, const int64_t
         g.count = (int)groups[key].size();
         g.blocks = 0;
         g.fblocks = 0;
+        g.two_pass_kinds = 0;
         g.fused_kinds = 0;
         g.oblocks = 0;
         g.any_outflow = false;
@@ -1015,7 +1031,7 @@ mclbm_status mclbm_batch_create(mclbm_sim *const *sims, int32_t n, const int64_t
             d.f[0] = s->f[0];
             d.f[1] = s->f[1];
             d.field = s->field;
-            d.gfield = s->gfield;
+            d.nfield = s->nfield;
             d.flag = s->d_flag;
             d.block0 = g.blocks;
             d.fblock0 = g.fblocks;
@@ -1026,10 +1042,12 @@ mclbm_status mclbm_batch_create(mclbm_sim *const *sims, int32_t n, const int64_t
                 const bool periodic = s->prm.bc[0] == MCLBM_PERIODIC && s->prm.bc[1] == MCLBM_PERIODIC
                                       && s->prm.bc[2] == MCLBM_PERIODIC;
                 g.fused_kinds |= fused_kind(periodic, s->prm.nx % kBatchTX != 0,
-                                            batch_wide(s->prm.precision, s->prm.model, s->prm.nx, s->prm.ny));
+                                            batch_wide(s->prm.precision, s->prm.model, s->prm.nx, s->prm.ny),
+                                            s->kp.far_rows != 0);
             } else {
                 d.nblocks = grid_of(s->kp.N);
                 g.blocks += d.nblocks;
+                g.two_pass_kinds |= s->kp.far ? kTwoPassFar : kTwoPassNear;
             }
             d.ocount = s->kp.has_outflow ? outflow_count(s->kp) : 0;
             d.oblock0 = g.oblocks;
@@ -1094,8 +1112,8 @@ static hipError_t batch_enqueue(mclbm_batch *b, int k)
         }
         for (size_t g = 0; g < G; ++g) {
             const auto &gr = b->groups[g];
-            gr.ops->batch_step(b->d_desc + gr.first, gr.count, gr.blocks, gr.fblocks, gr.fused_kinds, gr.oblocks,
-                               gr.any_outflow, g == 0 ? b->stream : b->side[g - 1]);
+            gr.ops->batch_step(b->d_desc + gr.first, gr.count, gr.blocks, gr.two_pass_kinds, gr.fblocks, gr.fused_kinds,
+                               gr.oblocks, gr.any_outflow, g == 0 ? b->stream : b->side[g - 1]);
         }
         for (size_t g = 1; g < G; ++g) {
             keep(hipEventRecord(b->join[g - 1], b->side[g - 1]));

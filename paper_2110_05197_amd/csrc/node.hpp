@@ -39,6 +39,8 @@ struct KParams {
     long long S;         // storage words from one population array to the next (>= N)
     int enhanced;
     int has_outflow;
+    int far;             // the arrays of one colour span 4 GB or more: 64-bit addressing
+    int far_rows;        // one-pass kernels with 64-bit addressing: far, or D3Q19 rows off the cache lines
     int conserve;        // CG, FP32 / mixed storage: keep each colour's node mass to one rounding
     double rho0[2];      // reference densities of the deviation storage
     double phi[2][3];    // CG: phi_i^k per group; SC: w per group

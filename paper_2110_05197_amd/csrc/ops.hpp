@@ -16,7 +16,7 @@ struct Ops {
     // blocks of the batched one-pass kernel the device holds at once (0: none)
     virtual long long batch_fused_resident() const = 0;
     // one step: src -> dst (the divergence flag reflects src)
-    virtual void step(const KParams &P, const void *src, void *dst, void *field, void *gfield,
+    virtual void step(const KParams &P, const void *src, void *dst, void *field, void *nfield,
                       unsigned *flag, bool fused, hipStream_t s) const = 0;
     virtual void density(const KParams &P, const void *f, void *field, unsigned *flag, hipStream_t s) const = 0;
     virtual void init(const KParams &P, const double *rR, const double *rB, const double *u, void *f,
@@ -29,8 +29,8 @@ struct Ops {
                      int nblocks, hipStream_t s) const = 0;
     // batched step over a group of descriptors: `blocks` two-pass blocks,
     // `fblocks` one-pass blocks, `oblocks` outflow blocks
-    virtual void batch_step(SimDesc *D, int n, long long blocks, long long fblocks, int fused_kinds, long long oblocks,
-                            bool any_outflow, hipStream_t s) const = 0;
+    virtual void batch_step(SimDesc *D, int n, long long blocks, int two_pass_kinds, long long fblocks,
+                            int fused_kinds, long long oblocks, bool any_outflow, hipStream_t s) const = 0;
     // interface observables: phase indicator of a node set, per-block red
     // fraction partial sums over a node set, initial component labels
     virtual void phase_sample(const KParams &P, const void *f, const NodeSet &ns, double *out,
@@ -50,6 +50,9 @@ inline long long outflow_count(const KParams &P)
     if (P.bc[2] == 2) c += 2LL * P.nx * P.ny;
     return c;
 }
+
+// Kinds of two-pass simulations in a batch group (KParams::far).
+constexpr int kTwoPassNear = 1, kTwoPassFar = 2;
 
 // REP: the model's extended force, which reaches beyond the one-node halo of
 // the one-pass kernels: the repulsion force of the colour-gradient model
@@ -88,7 +91,7 @@ struct OpsT final : Ops {
         return 0;
     }
 
-    void step(const KParams &P, const void *src, void *dst, void *field, void *gfield, unsigned *flag,
+    void step(const KParams &P, const void *src, void *dst, void *field, void *nfield, unsigned *flag,
               bool fused, hipStream_t s) const override
     {
         bool done = false;
@@ -100,17 +103,9 @@ struct OpsT final : Ops {
             }
         }
         if (!done) {
-            hipLaunchKernelGGL((k_density<L, PR, MODEL>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P,
-                               (const S *)src, (FT *)field, flag);
-            if constexpr (REP && MODEL == CG)
-                hipLaunchKernelGGL((k_gradN<L, PR>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P,
-                                   (const FT *)field, (FT *)gfield);
-            if constexpr (REP && MODEL == SC_MC && L::Q == 19)
-                hipLaunchKernelGGL((k_collide_mr<PR>), dim3((unsigned)mr_blocks(P)), dim3(kMrTX * kMrTY), 0, s, P,
-                                   (const S *)src, (S *)dst, (const FT *)field);
-            else
-                hipLaunchKernelGGL((k_collide<L, PR, MODEL, REP>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P,
-                                   (const S *)src, (S *)dst, (const FT *)field, (const FT *)gfield);
+            if (P.far) two_pass<true, false>(P, src, dst, field, nfield, flag, s);
+            else if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0) two_pass<false, true>(P, src, dst, field, nfield, flag, s);
+            else two_pass<false, false>(P, src, dst, field, nfield, flag, s);
         }
         if (P.has_outflow) {
             const long long c = outflow_count(P);
@@ -119,8 +114,25 @@ struct OpsT final : Ops {
     }
     void density(const KParams &P, const void *f, void *field, unsigned *flag, hipStream_t s) const override
     {
-        hipLaunchKernelGGL((k_density<L, PR, MODEL>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P,
-                           (const S *)f, (FT *)field, flag);
+        if (P.far) hipLaunchKernelGGL((k_density<L, PR, MODEL, true>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P, f, field, flag);
+        else hipLaunchKernelGGL((k_density<L, PR, MODEL, false>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P, f, field, flag);
+    }
+    template <bool FAR, bool PERIODIC>
+    static void two_pass(const KParams &P, const void *src, void *dst, void *field, void *nfield, unsigned *flag,
+                         hipStream_t s)
+    {
+        const dim3 grid(grid_of(P.N)), block(kBlock);
+        hipLaunchKernelGGL((k_density<L, PR, MODEL, FAR>), grid, block, 0, s, P, src, field, flag);
+        if constexpr (REP && MODEL == CG)
+            hipLaunchKernelGGL((k_normals<L, PR, FAR>), grid, block, 0, s, P, (const void *)field, nfield);
+        // FP32 takes the run-time push on periodic boxes too: the compile-time
+        // one spills 34 of its 128 registers (128^3 step 0.260 and 0.349 ms)
+        if constexpr (REP && MODEL == SC_MC && L::Q == 19)
+            hipLaunchKernelGGL((k_collide_mr<PR, FAR, PERIODIC && PR != 1>), dim3((unsigned)mr_blocks(P)), dim3(kMrTX * kMrTY), 0, s,
+                               P, src, dst, (const void *)field);
+        else
+            hipLaunchKernelGGL((k_collide<L, PR, MODEL, REP, FAR, PERIODIC>), grid, block, 0, s, P, src, dst,
+                               (const void *)field, (const void *)nfield);
     }
     void init(const KParams &P, const double *rR, const double *rB, const double *u, void *f,
               hipStream_t s) const override
@@ -164,18 +176,19 @@ struct OpsT final : Ops {
         hipLaunchKernelGGL((k_phase_labels<L, PR, MODEL>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P,
                            (const S *)f, labels);
     }
-    void batch_step(SimDesc *D, int n, long long blocks, long long fblocks, int fused_kinds, long long oblocks,
-                    bool any_outflow, hipStream_t s) const override
+    template <bool FAR>
+    static void batch_two_pass(SimDesc *D, int n, long long blocks, hipStream_t s)
     {
-        if (blocks > 0) {
-            hipLaunchKernelGGL((kb_density<L, PR, MODEL>), dim3((unsigned)blocks), dim3(kBlock), 0, s, D, n);
-            if constexpr (REP && MODEL == CG)
-                hipLaunchKernelGGL((kb_gradN<L, PR>), dim3((unsigned)blocks), dim3(kBlock), 0, s, D, n);
-            if constexpr (kb_collide_three_waves<L, PR, MODEL, REP>)
-                hipLaunchKernelGGL((kb_collide_w3<L, PR, MODEL, REP>), dim3((unsigned)blocks), dim3(kBlock), 0, s, D, n);
-            else
-                hipLaunchKernelGGL((kb_collide<L, PR, MODEL, REP>), dim3((unsigned)blocks), dim3(kBlock), 0, s, D, n);
-        }
+        const dim3 grid((unsigned)blocks), block(kBlock);
+        hipLaunchKernelGGL((kb_density<L, PR, MODEL, FAR>), grid, block, 0, s, D, n);
+        if constexpr (REP && MODEL == CG) hipLaunchKernelGGL((kb_normals<L, PR, FAR>), grid, block, 0, s, D, n);
+        hipLaunchKernelGGL((kb_collide<L, PR, MODEL, REP, FAR>), grid, block, 0, s, D, n);
+    }
+    void batch_step(SimDesc *D, int n, long long blocks, int two_pass_kinds, long long fblocks, int fused_kinds,
+                    long long oblocks, bool any_outflow, hipStream_t s) const override
+    {
+        if (two_pass_kinds & kTwoPassNear) batch_two_pass<false>(D, n, blocks, s);
+        if (two_pass_kinds & kTwoPassFar) batch_two_pass<true>(D, n, blocks, s);
         if constexpr (batch_fused_available<L, PR, MODEL, REP>()) {
             if (fblocks > 0) launch_batch_fused<PR, MODEL>(D, n, fblocks, fused_kinds, s);
         }
