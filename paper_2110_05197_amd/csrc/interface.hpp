@@ -66,13 +66,27 @@ __global__ __launch_bounds__(kBlock) void k_phase_area(KParams P, const typename
     }
 }
 
-// Initial component labels: own node index inside the red phase, -1 outside.
+// Initial component labels: -1 outside the red phase, inside it the first node
+// of the node's run along x within its wave (runs end at the row's end), which
+// joins the lanes of a run without touching memory.  Also clears the sizes and
+// the component count of the passes that follow.
 template <class L, int PR, int MODEL>
 __global__ __launch_bounds__(kBlock) void k_phase_labels(KParams P, const typename Prec<PR>::S *__restrict__ f,
-                                                         int *__restrict__ labels)
+                                                         int *__restrict__ labels, int *__restrict__ sizes,
+                                                         int *__restrict__ count)
 {
-    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (n < P.N) labels[n] = node_phase64<L, PR, MODEL>(P, f, n) > 0.0 ? (int)n : -1;
+    const unsigned n = blockIdx.x * (unsigned)kBlock + threadIdx.x;
+    const bool in_box = n < (unsigned)P.N;
+    const bool inside = in_box && node_phase64<L, PR, MODEL>(P, f, n) > 0.0;
+    const unsigned long long in = __ballot(inside), row = __ballot(n % (unsigned)P.nx == 0);
+    const int lane = (int)(threadIdx.x & 63);
+    // lanes that start a run: inside, and the lane before is outside or of another row
+    const unsigned long long starts = in & (~(in << 1) | row | 1ull);
+    if (n == 0) *count = 0;
+    if (!in_box) return;
+    sizes[n] = 0;
+    const int start = 63 - __clzll((long long)(starts & (~0ull >> (63 - lane))));
+    labels[n] = inside ? (int)n - (lane - start) : -1;
 }
 
 }  // namespace mclbm

@@ -37,7 +37,8 @@ struct Ops {
                               hipStream_t s) const = 0;
     virtual void phase_area(const KParams &P, const void *f, const NodeSet &ns, double *partials, int nblocks,
                             hipStream_t s) const = 0;
-    virtual void phase_labels(const KParams &P, const void *f, int *labels, hipStream_t s) const = 0;
+    virtual void phase_labels(const KParams &P, const void *f, int *labels, int *sizes, int *count,
+                              hipStream_t s) const = 0;
 };
 
 inline unsigned grid_of(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -171,10 +172,11 @@ struct OpsT final : Ops {
         hipLaunchKernelGGL((k_phase_area<L, PR, MODEL>), dim3(nblocks), dim3(kBlock), 0, s, P, (const S *)f, ns,
                            partials);
     }
-    void phase_labels(const KParams &P, const void *f, int *labels, hipStream_t s) const override
+    void phase_labels(const KParams &P, const void *f, int *labels, int *sizes, int *count,
+                      hipStream_t s) const override
     {
         hipLaunchKernelGGL((k_phase_labels<L, PR, MODEL>), dim3(grid_of(P.N)), dim3(kBlock), 0, s, P,
-                           (const S *)f, labels);
+                           (const S *)f, labels, sizes, count);
     }
     template <bool FAR>
     static void batch_two_pass(SimDesc *D, int n, long long blocks, hipStream_t s)
