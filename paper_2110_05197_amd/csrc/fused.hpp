@@ -40,6 +40,52 @@ __device__ __forceinline__ void field_values(const HP<C, M> &H, const M (&dr)[2]
     }
 }
 
+// Collision of one node from the stencil values of its neighbours
+// (v[field][direction], field_values order) and, for SC multiphase, its own
+// pseudopotential; c holds its populations, dr and j their moments.
+template <class L, int MODEL, int CONS, int NF, int K, class C, class M>
+__device__ __forceinline__ void collide_values(const HP<C, M> &H, C (&c)[K][L::Q], const M (&dr)[2], const M (&j)[3],
+                                               const C (&v)[NF][L::Q], C psi)
+{
+    if constexpr (MODEL == CG) {
+        C gR[3], gB[3], gN[3];
+        stencil_sum<L>(v[0], gR);
+        stencil_sum<L>(v[1], gB);
+        stencil_sum<L>(v[NF - 1], gN);
+#pragma unroll
+        for (int dd = 0; dd < 3; ++dd) { gR[dd] *= C(3); gB[dd] *= C(3); gN[dd] *= C(3); }
+        const C F0[3] = {C(0), C(0), C(0)};
+        cg_collide<L, C, M, false, CONS>(H, c, dr, j, gR, gB, gN, F0);
+    } else if constexpr (MODEL == SC_MP) {
+        C s3[3];
+        stencil_sum<L>(v[0], s3);
+        const M rho = H.rho0[0] + dr[0];
+        const M irho = rcp(rho);
+        C F[3], u[3];
+#pragma unroll
+        for (int dd = 0; dd < 3; ++dd) {
+            F[dd] = -H.G * psi * s3[dd];
+            u[dd] = (C)((j[dd] + M(0.5) * (M)F[dd]) * irho);
+        }
+        sc_collide_component<L, C, M>(c[0], H.om[0], dr[0], rho, u, F, H.rho0[0], H.corrM[0], H.shiftM[0]);
+    } else {
+        C sR[3], sB[3];
+        stencil_sum<L>(v[0], sR);
+        stencil_sum<L>(v[NF - 1], sB);
+        const M rR = H.rho0[0] + dr[0], rB = H.rho0[1] + dr[1];
+        const M ir = rcp(rR + rB);
+        C FR[3], FB[3], u[3];
+#pragma unroll
+        for (int dd = 0; dd < 3; ++dd) {
+            FR[dd] = -H.xpref * (C)rR * sB[dd];
+            FB[dd] = -H.xpref * (C)rB * sR[dd];
+            u[dd] = (C)((j[dd] + M(0.5) * ((M)FR[dd] + (M)FB[dd])) * ir);
+        }
+        sc_collide_component<L, C, M>(c[0], H.om[0], dr[0], rR, u, FR, H.rho0[0], H.corrM[0], H.shiftM[0]);
+        sc_collide_component<L, C, M>(c[K - 1], H.om[1], dr[1], rB, u, FB, H.rho0[1], H.corrM[1], H.shiftM[1]);
+    }
+}
+
 // Block index -> tile, keeping runs of consecutive tiles on one XCD (blocks
 // are dealt round-robin to the 8 XCDs, each with its own L2).
 __device__ __forceinline__ int xcd_tile(int b, int nblocks)
@@ -229,44 +275,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
 #pragma unroll
             for (int a = 0; a < NF; ++a) v[a][0] = C(0);
 
-            if constexpr (MODEL == CG) {
-                C gR[3], gB[3], gN[3];
-                stencil_sum<L>(v[0], gR);
-                stencil_sum<L>(v[1], gB);
-                stencil_sum<L>(v[NF - 1], gN);
-#pragma unroll
-                for (int dd = 0; dd < 3; ++dd) { gR[dd] *= C(3); gB[dd] *= C(3); gN[dd] *= C(3); }
-                const C F0[3] = {C(0), C(0), C(0)};
-                cg_collide<L, C, M, false, CONS>(H, c, drc, jc, gR, gB, gN, F0);
-            } else if constexpr (MODEL == SC_MP) {
-                C s3[3];
-                stencil_sum<L>(v[0], s3);
-                const C psi = (C)lds[ring(z)][0][my_slot];
-                const M rho = H.rho0[0] + drc[0];
-                const M irho = rcp(rho);
-                C F[3], u[3];
-#pragma unroll
-                for (int dd = 0; dd < 3; ++dd) {
-                    F[dd] = -H.G * psi * s3[dd];
-                    u[dd] = (C)((jc[dd] + M(0.5) * (M)F[dd]) * irho);
-                }
-                sc_collide_component<L, C, M>(c[0], H.om[0], drc[0], rho, u, F, H.rho0[0], H.corrM[0], H.shiftM[0]);
-            } else {
-                C sR[3], sB[3];
-                stencil_sum<L>(v[0], sR);
-                stencil_sum<L>(v[NF - 1], sB);
-                const M rR = H.rho0[0] + drc[0], rB = H.rho0[1] + drc[1];
-                const M ir = rcp(rR + rB);
-                C FR[3], FB[3], u[3];
-#pragma unroll
-                for (int dd = 0; dd < 3; ++dd) {
-                    FR[dd] = -H.xpref * (C)rR * sB[dd];
-                    FB[dd] = -H.xpref * (C)rB * sR[dd];
-                    u[dd] = (C)((jc[dd] + M(0.5) * ((M)FR[dd] + (M)FB[dd])) * ir);
-                }
-                sc_collide_component<L, C, M>(c[0], H.om[0], drc[0], rR, u, FR, H.rho0[0], H.corrM[0], H.shiftM[0]);
-                sc_collide_component<L, C, M>(c[K - 1], H.om[1], drc[1], rB, u, FB, H.rho0[1], H.corrM[1], H.shiftM[1]);
-            }
+            collide_values<L, MODEL, CONS>(H, c, drc, jc, v, MODEL == SC_MP ? (C)lds[ring(z)][0][my_slot] : C(0));
             const unsigned n = n_xy + sxy * (unsigned)z;
             // populations that stay on their x (cx = 0) land on whole cache
             // lines and are never read again in this step: stream them past

@@ -539,6 +539,7 @@ struct mclbm_sim {
     hipStream_t stream;
     int device;
     bool fused;
+    int tile;          // small D2Q9 box, automatic kernel choice: most steps a tile launch takes (0: none)
     bool in_batch;
     unsigned *d_flag;
     double *d_partials;
@@ -715,6 +716,9 @@ mclbm_status mclbm_create(const mclbm_params *p, void *d_state, size_t bytes, vo
     sim->stream = (hipStream_t)stream;
     sim->fused = p->kernel != MCLBM_KERNEL_TWO_PASS && fused_ok(*p, sim->ops)
                  && (p->kernel == MCLBM_KERNEL_FUSED || auto_prefers_fused(*p));
+    // the two-pass step of a box whose kernel was left to the library runs as
+    // one launch over tiles
+    sim->tile = p->kernel == MCLBM_KERNEL_AUTO && !sim->fused ? sim->ops->tile_steps(sim->kp) : 0;
     sim->in_batch = false;
     hipError_t e = hipGetDevice(&sim->device);
     if (e == hipSuccess) e = hipMalloc((void **)&sim->d_flag, 256);
@@ -819,21 +823,32 @@ mclbm_status mclbm_step(mclbm_sim *sim, int64_t nsteps, int64_t check_every, int
     if (s) return s;
     if (nsteps < 0 || check_every < 0) return fail(MCLBM_EINVAL, "negative step count");
     int64_t done = 0;
-    for (int64_t t = 0; t < nsteps; ++t) {
-        sim->ops->step(sim->kp, sim->f[sim->cur], sim->f[sim->cur ^ 1], sim->field, sim->nfield, sim->d_flag,
-                       sim->fused, sim->stream);
-        sim->cur ^= 1;
-        ++sim->step;
-        ++done;
-        if (check_every > 0 && (done % check_every == 0 || t + 1 == nsteps)) {
+    while (done < nsteps) {
+        // steps up to the next check.  Launches of two steps go in pairs, so
+        // that the current buffer after a number of steps is the same as with
+        // launches of one.
+        int64_t run = nsteps - done;
+        if (check_every > 0) run = std::min(run, check_every - done % check_every);
+        for (int64_t t = 0; t < run;) {
+            const int k = sim->tile == 2 && run - t >= 4 ? 4 : 1;
+            for (int launch = 0; launch < (k == 4 ? 2 : 1); ++launch) {
+                const void *src = sim->f[sim->cur];
+                void *dst = sim->f[sim->cur ^ 1];
+                if (sim->tile) sim->ops->tile_step(sim->kp, src, dst, sim->d_flag, k == 4 ? 2 : 1, sim->stream);
+                else sim->ops->step(sim->kp, src, dst, sim->field, sim->nfield, sim->d_flag, sim->fused, sim->stream);
+                sim->cur ^= 1;
+            }
+            t += k;
+        }
+        done += run;
+        sim->step += run;
+        if (check_every > 0) {
             s = launched("step");
-            if (s) { if (steps_done) *steps_done = done; return s; }
             int32_t dv = 0;
-            s = mclbm_diverged(sim, &dv);
-            if (s) { if (steps_done) *steps_done = done; return s; }
-            if (dv) {
+            if (!s) s = mclbm_diverged(sim, &dv);
+            if (s || dv) {
                 if (steps_done) *steps_done = done;
-                return MCLBM_DIVERGED;
+                return s ? s : MCLBM_DIVERGED;
             }
         }
     }

@@ -18,6 +18,11 @@ struct Ops {
     // one step: src -> dst (the divergence flag reflects src)
     virtual void step(const KParams &P, const void *src, void *dst, void *field, void *nfield,
                       unsigned *flag, bool fused, hipStream_t s) const = 0;
+    // small-box tile kernels: most steps a launch takes (0: none), and one
+    // launch of `steps` (1 or 2) steps
+    virtual int tile_steps(const KParams &P) const = 0;
+    virtual void tile_step(const KParams &P, const void *src, void *dst, unsigned *flag, int steps,
+                           hipStream_t s) const = 0;
     virtual void density(const KParams &P, const void *f, void *field, unsigned *flag, hipStream_t s) const = 0;
     virtual void init(const KParams &P, const double *rR, const double *rB, const double *u, void *f,
                       hipStream_t s) const = 0;
@@ -75,6 +80,10 @@ template <int PR, int MODEL>
 void launch_fused(const KParams &P, const void *src, void *dst, unsigned *flag, hipStream_t s);
 template <int PR, int MODEL>
 void launch_fused2d(const KParams &P, const void *src, void *dst, unsigned *flag, hipStream_t s);
+template <int PR>
+int tile2d_steps(const KParams &P);
+template <int PR, int MODEL>
+void launch_tile2d(const KParams &P, const void *src, void *dst, unsigned *flag, int steps, hipStream_t s);
 template <int PR, int MODEL>
 void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStream_t s);
 template <int PR, int MODEL>
@@ -108,6 +117,21 @@ struct OpsT final : Ops {
             else if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0) two_pass<false, true>(P, src, dst, field, nfield, flag, s);
             else two_pass<false, false>(P, src, dst, field, nfield, flag, s);
         }
+        outflow(P, dst, s);
+    }
+    int tile_steps(const KParams &P) const override
+    {
+        if constexpr (L::Q == 9 && !REP) return tile2d_steps<PR>(P);
+        return 0;
+    }
+    void tile_step(const KParams &P, const void *src, void *dst, unsigned *flag, int steps, hipStream_t s) const override
+    {
+        if constexpr (L::Q == 9 && !REP) launch_tile2d<PR, MODEL>(P, src, dst, flag, steps, s);
+        outflow(P, dst, s);
+    }
+    // entering populations of the outflow faces
+    static void outflow(const KParams &P, void *dst, hipStream_t s)
+    {
         if (P.has_outflow) {
             const long long c = outflow_count(P);
             hipLaunchKernelGGL((k_outflow<L, PR, MODEL>), dim3(grid_of(c)), dim3(kBlock), 0, s, P, (S *)dst, c);
