@@ -92,8 +92,9 @@ typedef int32_t mclbm_status;
 #define MCLBM_OUTFLOW 2
 
 /* Kernel choice for mclbm_step. */
-#define MCLBM_KERNEL_AUTO 0     /* fused where provided (D2Q9: from 2^19 nodes;    */
-                                /* below, the two passes in one launch over tiles) */
+#define MCLBM_KERNEL_AUTO 0     /* the faster: D3Q19 one pass, or two passes where */
+                                /* its columns would idle; D2Q9 one pass from 2^19 */
+                                /* nodes, below both passes in a launch over tiles */
 #define MCLBM_KERNEL_TWO_PASS 1 /* density-field pass + collide/stream pass       */
 #define MCLBM_KERNEL_FUSED 2    /* one pass per step: CG/SC without repulsion     */
 
@@ -312,9 +313,10 @@ mclbm_status mclbm_droplets(mclbm_sim *sim, int32_t max, int32_t *count, int64_t
 
 /* The step kernel this simulation runs: MCLBM_KERNEL_FUSED (one pass:
  * without the repulsion or multirange forces; D3Q19 with ny % 4 == 0 and any
- * nx, D2Q9 of any size) or MCLBM_KERNEL_TWO_PASS (also small D2Q9 boxes left to
- * the automatic choice, whose two passes run in one launch over tiles, two
- * steps a launch where periodic).  Host only; EINVAL on NULL. */
+ * nx, and under the automatic choice large boxes of any ny; D2Q9 of any size)
+ * or MCLBM_KERNEL_TWO_PASS (also small D2Q9 boxes left to the automatic choice,
+ * whose two passes run in one launch over tiles, two steps a launch where
+ * periodic).  Host only; EINVAL on NULL. */
 mclbm_status mclbm_kernel_used(const mclbm_sim *sim, int32_t *kernel);
 
 /* Work of one block of the one-pass kernel: a *tx x *ty column of nodes

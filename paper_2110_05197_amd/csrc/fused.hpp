@@ -150,8 +150,8 @@ template <int PR, bool YH> constexpr bool kPointerLoads = (PR == 1 && !YH) || (P
 // operation.  CONS: whether the collision keeps each colour's node mass
 // (kConsNever / kConsAsked / kConsAlways, see cg_collide): the batched
 // kernels ask each simulation, the solo launches choose a kernel.
-template <int PR, int MODEL, int TX, int TY, bool PERIODIC, bool EDGE = false, class L = D3Q19, class LA = L,
-          int CONS = kConsShared<PR>, bool FAR = false>
+template <int PR, int MODEL, int TX, int TY, bool PERIODIC, int EDGE = 0, class L = D3Q19, class LA = L,
+          int CONS = kConsShared<PR>, bool FAR = false, bool SPREAD = true>
 __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp, void *dstp, unsigned *flag, int x0,
                                              int y0, int z0, int z1, unsigned char *smem)
 {
@@ -182,18 +182,19 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
     const int lx = tid % TX, ly = tid / TX;
     const int x = x0 + lx, y = y0 + ly;
     const int my_slot = (ly + RY) * HX + (lx + 1);
-    const int w = EDGE ? min(TX, nx - x0) : TX;   // nodes per row of this column
-    const bool act = !EDGE || lx < w;
+    const int w = EDGE ? min(TX, nx - x0) : TX;        // nodes per row of this column
+    const int h = EDGE == 2 ? min(TY, ny - y0) : TY;   // rows of this column
+    const bool act = (!EDGE || lx < w) && (EDGE != 2 || ly < h);
 
-    // halo ring node of this thread: rows y0-1 and y0+TY (when the lattice
+    // halo ring node of this thread: rows y0-1 and y0+h (when the lattice
     // has y velocities), then columns x0-1 and x0+w
     constexpr int NR = YH ? 2 * HX : 0;
     int hx = 0, hy = 0;
     if (YH && tid < HX) { hx = tid - 1; hy = -1; }
-    else if (YH && tid < NR) { hx = tid - HX - 1; hy = TY; }
+    else if (YH && tid < NR) { hx = tid - HX - 1; hy = h; }
     else if (tid < NR + TY) { hx = -1; hy = tid - NR; }
     else { hx = w; hy = tid - NR - TY; }
-    const bool has_h = tid < NH && hx <= w;
+    const bool has_h = tid < NH && hx <= w && (EDGE != 2 || hy <= h);
     const int h_slot = (hy + RY) * HX + (hx + 1);
     const int hgx = stencil_coord(x0 + hx, nx, P.bc[0]);
     const int hgy = stencil_coord(y0 + hy, ny, P.bc[1]);
@@ -251,7 +252,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
         // rows 4096^2 FP32 0.489 -> 0.480 ms, buffer loads at 256^3 FP32 1.155
         // -> 1.085 ms, 64-bit addressed columns on ragged rows 234 x 80 x 119
         // FP32 0.223 -> 0.217.
-        constexpr int spacing = FAR ? 0 : kLoadSpacing<PR, MODEL, YH>;
+        constexpr int spacing = FAR || !SPREAD ? 0 : kLoadSpacing<PR, MODEL, YH>;
         const bool ahead = z + 2 <= z1;
         RawNode<L, K, S, C> dr_, hr_;
         __builtin_amdgcn_s_setprio(3);
@@ -329,7 +330,10 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
 // The columns of a launch in x: all full (TX divides nx), the last one an edge
 // column, or one edge column only (nx < TX; a kernel of its own holds a single
 // column body: 27 x 32 x 230 mixed 0.0385 -> 0.0362 ms).
-constexpr int kColsFull = 0, kColsRagged = 1, kColsNarrow = 2;
+// Or, for boxes whose rows no column height divides, the last column in x and in
+// y edge columns of both kinds (near addressing, loads not spread: such boxes'
+// rows are seldom line-aligned).
+constexpr int kColsFull = 0, kColsRagged = 1, kColsNarrow = 2, kColsOdd = 3;
 template <int PR, int MODEL, int TX, int TY, bool PERIODIC, int COLS, class L, class LA, bool CONS, bool FAR>
 __global__ __launch_bounds__(TX *TY) void k_fused(KParams P, const void *src, void *dst, unsigned *flag, int TZ,
                                                   int tiles_x, int tiles_y)
@@ -339,13 +343,18 @@ __global__ __launch_bounds__(TX *TY) void k_fused(KParams P, const void *src, vo
     const int bx = t % tiles_x, by = (t / tiles_x) % tiles_y, bz = t / (tiles_x * tiles_y);
     const int x0 = bx * TX, y0 = by * TY, z0 = bz * TZ, z1 = min(z0 + TZ, P.nz);
     constexpr int cons = CONS ? kConsAlways : kConsNever;
-    if constexpr (COLS != kColsFull) {
+    if constexpr (COLS == kColsOdd) {
+        if (bx == tiles_x - 1 || by == tiles_y - 1) {
+            fused_column<PR, MODEL, TX, TY, PERIODIC, 2, L, LA, cons, FAR, false>(P, src, dst, flag, x0, y0, z0, z1, smem);
+            return;
+        }
+    } else if constexpr (COLS != kColsFull) {
         if (COLS == kColsNarrow || bx == tiles_x - 1) {
-            fused_column<PR, MODEL, TX, TY, PERIODIC, true, L, LA, cons, FAR>(P, src, dst, flag, x0, y0, z0, z1, smem);
+            fused_column<PR, MODEL, TX, TY, PERIODIC, 1, L, LA, cons, FAR>(P, src, dst, flag, x0, y0, z0, z1, smem);
             return;
         }
     }
-    fused_column<PR, MODEL, TX, TY, PERIODIC, false, L, LA, cons, FAR>(P, src, dst, flag, x0, y0, z0, z1, smem);
+    fused_column<PR, MODEL, TX, TY, PERIODIC, 0, L, LA, cons, FAR, COLS != kColsOdd>(P, src, dst, flag, x0, y0, z0, z1, smem);
 }
 
 // Batched one-pass step: the blocks of all eligible simulations of a group
@@ -433,7 +442,7 @@ __global__ __launch_bounds__(kb_tx(WIDE) * kb_ty(PR, WIDE)) void kb_fused(SimDes
     const int bx = (int)(b % tiles_x), by = (int)((b / tiles_x) % tiles_y), bz = (int)(b / ((long long)tiles_x * tiles_y));
     const int x0 = bx * TX, y0 = by * TY, z0 = bz * d.ftz, z1 = min(z0 + d.ftz, d.P.nz);
     unsigned *flag = global_ptr<unsigned>(d.flag);
-    fused_column<PR, MODEL, TX, TY, PERIODIC, EDGE, D3Q19, D3Q19, kConsShared<PR>, FAR>(
+    fused_column<PR, MODEL, TX, TY, PERIODIC, EDGE ? 1 : 0, D3Q19, D3Q19, kConsShared<PR>, FAR>(
         d.P, global_ptr<char>(d.f[d.cur]), global_ptr<char>(d.f[d.cur ^ 1]), flag, x0, y0, z0, z1, smem);
 }
 
@@ -545,7 +554,59 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 struct FusedShape {
     int tx, ty, tz;
     bool ragged;   // the last column in x is an edge column
+    bool odd;      // the last column in x and in y may be (no column height divides ny)
 };
+
+// What a one-pass step of this shape does beyond its nodes' work, as a factor:
+// idle lanes of edge columns, three planes of loads per chunk before the march
+// starts, compute units (256 on MI355X, one block each) left idle.
+inline double fused_overhead(const KParams &P, const FusedShape &sh)
+{
+    const long long tiles_x = (P.nx + sh.tx - 1) / sh.tx, tiles_y = (P.ny + sh.ty - 1) / sh.ty;
+    const long long chunks = (P.nz + sh.tz - 1) / sh.tz, blocks = tiles_x * tiles_y * chunks;
+    const double lanes = (double)(tiles_x * sh.tx) * (double)(tiles_y * sh.ty) / ((double)P.nx * P.ny);
+    const double fill = (double)((blocks + 255) / 256 * 256) / (double)blocks;
+    return lanes * fill * (sh.tz + 3) / sh.tz;
+}
+
+// z-chunks: at most one block per compute unit -- more resident blocks per XCD
+// overflow its L2 and the halo re-reads miss, and a grid just above 256 blocks
+// runs a second, nearly empty round.  Where that leaves too many units idle,
+// the chunk length with the least rounds * (planes + 3) instead: FP64 176^3,
+// 132 columns, 1.34 -> 0.95 ms, 192^3 1.43 -> 1.04, 200^3 (200 blocks) 1.66 ->
+// 1.48; FP32 gains less from filling up (176^3, 198 blocks, 0.549 -> 0.520)
+// and loses from 200 blocks on (200^3 0.860 -> 0.916).
+inline void fused_chunks(const KParams &P, FusedShape &sh, bool wide)
+{
+    const long long txy = (long long)((P.nx + sh.tx - 1) / sh.tx) * ((P.ny + sh.ty - 1) / sh.ty);
+    const long long tiles_z = std::max<long long>(1, 256 / txy);
+    sh.tz = (int)((P.nz + tiles_z - 1) / tiles_z);
+    const long long blocks = txy * ((P.nz + sh.tz - 1) / sh.tz);
+    if (blocks >= (wide ? 204 : 199) || txy * P.nz < 256) return;
+    long long best = -1;
+    for (int chunks = 1; chunks <= P.nz; ++chunks) {
+        const int tz = (P.nz + chunks - 1) / chunks;
+        const long long rounds = (txy * ((P.nz + tz - 1) / tz) + 255) / 256;
+        if (best < 0 || rounds * (tz + 3) < best) {
+            best = rounds * (tz + 3);
+            sh.tz = tz;
+        }
+    }
+}
+
+// The automatic choice for D3Q19 boxes whose ny 4 does not divide: one-pass
+// columns with edge columns in y too where they have little to spare (128 x 126
+// x 128, overhead 1.2: FP32 0.212 -> 0.161 ms, FP64 0.418 -> 0.302; 190 x 57 x
+// 120, 1.5: 0.136 and 0.133).
+inline bool fused_odd_shape(const KParams &P, FusedShape &sh, bool wide)
+{
+    sh.tx = 64;
+    sh.ty = wide ? 4 : 8;
+    sh.ragged = true;
+    sh.odd = true;
+    fused_chunks(P, sh, wide);
+    return P.ny % 4 != 0 && !P.far && !P.conserve && P.N >= (1 << 18) && fused_overhead(P, sh) < 1.3;
+}
 
 // Tile choice: 64-wide rows (narrower rows split the x-shifted pushes' cache
 // lines between blocks), the last column masked when 64 does not divide nx;
@@ -566,13 +627,32 @@ inline bool fused_shape(const KParams &P, FusedShape &sh, bool wide = false)
     } else if (!wide && P.ny % 8 == 0) sh.ty = 8;
     else if (P.ny % 4 == 0) sh.ty = 4;
     else return false;
-    // z-chunk: at most one block per compute unit (256 on MI355X) -- more
-    // resident blocks per XCD overflow its L2 and the halo re-reads miss,
-    // and a grid just above 256 blocks runs a second, nearly empty round
-    const long long txy = (long long)((P.nx + sh.tx - 1) / sh.tx) * (P.ny / sh.ty);
-    const long long tiles_z = std::max<long long>(1, 256 / txy);
-    sh.tz = (int)((P.nz + tiles_z - 1) / tiles_z);
+    sh.odd = false;
+    fused_chunks(P, sh, wide);
     return true;
+}
+
+// Automatic choice between the one-pass and the two-pass kernels on D3Q19,
+// where both exist: two-pass where the one-pass shape's overhead (64 x 4
+// columns, half the waves a unit, weighted) is past a line per precision.  FP32
+// colour gradient, one-pass and two-pass us: 80 x 40 x 150 (overhead 2.5) 60.6
+// and 42.1, 72^3 (3.2) 45.4 and 35.9, 100^3 (64 x 4 columns, 2.0) 125 and 88,
+// 64^3 (2.5) 24.7 and 23.0, 128 x 64 x 64 (1.75) 42.8 and 45.3, 144^3 (1.7) 311
+// and 322, 128^3 (1.2) 149 and 205.  FP64 72^3 (2.3) 112 and 65, 48 x 96 x 100
+// (1.85) 84 and 82, 100^3 (1.5) 200 and 210.  Mixed, whose one-pass kernel is
+// the shortest of registers: 64 x 32 x 200 42.6 and 36.6, 128 x 64 x 64 48.1
+// and 47.4, 256 x 64 x 64 (1.4) 86 and 100.  FP16 storage, 64^3 16.1 and 17.7,
+// 100^3 75 and 51.  Boxes of a few thousand nodes take 8-15 us either way.
+inline bool d3_prefers_two_pass(const KParams &P, int precision, int model)
+{
+    FusedShape sh;
+    if (!fused_shape(P, sh, precision == 0)) return false;
+    const long long least = precision == 2 ? 1 << 14 : model == SC_MP ? 1 << 18 : 1 << 16;
+    if (P.N < least || P.conserve) return false;
+    const bool low = precision != 0 && sh.tx == 64 && sh.ty == 4;
+    const double weight = !low ? 1.0 : precision == 3 ? 1.8 : 1.35;
+    const double line = precision == 0 ? 1.9 : precision == 2 ? 1.73 : precision == 3 ? 2.6 : 2.0;
+    return weight * fused_overhead(P, sh) > line;
 }
 
 // One launch of k_fused; the dynamic-LDS limit is raised once per kernel and
@@ -629,7 +709,15 @@ void launch_fused_shape(const KParams &P, const void *src, void *dst, unsigned *
 template <int PR, int MODEL, int TY>
 void launch_fused_cols(const KParams &P, const FusedShape &sh, const void *src, void *dst, unsigned *flag, hipStream_t s)
 {
-    if (!sh.ragged) launch_fused_shape<PR, MODEL, 64, TY, kColsFull>(P, src, dst, flag, sh.tz, s);
+    if (sh.odd) {
+        const int tiles_x = (P.nx + 63) / 64, tiles_y = (P.ny + TY - 1) / TY;
+        if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0)
+            launch_fused_one<PR, MODEL, 64, TY, true, kColsOdd, D3Q19, D3Q19, false, false>(P, src, dst, flag, sh.tz,
+                                                                                           tiles_x, tiles_y, s);
+        else
+            launch_fused_one<PR, MODEL, 64, TY, false, kColsOdd, D3Q19, D3Q19, false, false>(P, src, dst, flag, sh.tz,
+                                                                                            tiles_x, tiles_y, s);
+    } else if (!sh.ragged) launch_fused_shape<PR, MODEL, 64, TY, kColsFull>(P, src, dst, flag, sh.tz, s);
     else if (P.nx > 64) launch_fused_shape<PR, MODEL, 64, TY, kColsRagged>(P, src, dst, flag, sh.tz, s);
     else launch_fused_shape<PR, MODEL, 64, TY, kColsNarrow>(P, src, dst, flag, sh.tz, s);
 }
@@ -638,13 +726,14 @@ template <int PR, int MODEL>
 void launch_fused(const KParams &P, const void *src, void *dst, unsigned *flag, hipStream_t s)
 {
     FusedShape sh;
-    fused_shape(P, sh, PR == 0);  // checked at create time
+    if (!fused_shape(P, sh, PR == 0)) fused_odd_shape(P, sh, PR == 0);  // checked at create time
     if constexpr (PR != 0) {
         if (sh.tx == 96) {
             launch_fused_shape<PR, MODEL, 96, 4, kColsFull>(P, src, dst, flag, sh.tz, s);
             return;
         }
     }
+    // (one column height per precision for odd boxes)
     if (sh.ty == 4) launch_fused_cols<PR, MODEL, 4>(P, sh, src, dst, flag, s);
     else if constexpr (PR != 0) launch_fused_cols<PR, MODEL, 8>(P, sh, src, dst, flag, s);
 }

@@ -131,12 +131,13 @@ bool fused_ok(const mclbm_params &p, const Ops *ops)
 }
 
 // Automatic kernel choice where both exist: the one-pass kernel, except on
-// D2Q9 boxes under 2^19 nodes, whose few short rows leave the one-pass
-// kernel latency-bound (512^2: 0.81x, 64^2: 0.33x of the two-pass speed;
-// 1000^2: 1.21x, 4096^2: 1.59x).
+// D2Q9 boxes under 2^19 nodes, whose few short rows leave the marching kernel
+// latency-bound (they step on tiles instead), and on D3Q19 boxes whose columns
+// would have too much to spare (d3_prefers_two_pass).
 bool auto_prefers_fused(const mclbm_params &p)
 {
-    return p.lattice != MCLBM_D2Q9 || (long long)p.nx * p.ny >= (1LL << 19);
+    if (p.lattice == MCLBM_D2Q9) return (long long)p.nx * p.ny >= (1LL << 19);
+    return !d3_prefers_two_pass(make_kparams(p), p.precision, p.model);
 }
 
 // The batched one-pass kernel takes 96 x 4 columns where 96 divides nx and
@@ -239,20 +240,28 @@ KParams make_kparams(const mclbm_params &p)
     for (int d = 0; d < 3; ++d) K.bc[d] = p.bc[d];
     K.N = (long long)p.nx * p.ny * p.nz;
     K.S = pop_stride(p);
-    // the buffer resources of the step kernels hold byte offsets in 32 bits
+    // the step kernels' buffer resources hold byte offsets in 32 bits
     K.far = (unsigned long long)lattice_Q(p.lattice) * (unsigned long long)K.S * pop_word(p) >= (1ull << 32) ? 1 : 0;
-    // D3Q19 rows that do not start on a cache line each: the one-pass kernels'
-    // lines are then shared by the rows above and below, and tightly issued
-    // buffer loads miss what the pointer loads, spaced by their address
-    // arithmetic, find in L2.  FP32, pointers and buffers (ms per step):
-    // 234 x 80 x 119 colour gradient 0.218 and 0.230, 201 x 160 x 170 0.588
-    // and 0.602; on line-aligned rows 160^3 0.357 and 0.331, 192^3 with walls
-    // 0.68 and 0.616.  FP16 storage gains either way (250 x 120 x 101: 0.166
-    // and 0.155), and so do boxes of one column (27 x 32 x 230 FP32: 0.0304
-    // and 0.0275).
+    // One-pass D3Q19 columns keep 64-bit addressing also
+    // - in FP32 and mixed where rows do not start on a cache line each: lines
+    //   are then shared by the rows above and below, and tightly issued buffer
+    //   loads miss what the pointer loads, spaced by their address arithmetic,
+    //   find in L2 (FP32, pointers and buffers, ms per step: 234 x 80 x 119
+    //   colour gradient 0.218 and 0.230, 201 x 160 x 170 0.588 and 0.602; on
+    //   line-aligned rows 160^3 0.357 and 0.331, 192^3 with walls 0.68 and
+    //   0.616).  FP16 storage gains either way (250 x 120 x 101: 0.166 and
+    //   0.155), and so do boxes of one column (27 x 32 x 230 FP32: 0.0304 and
+    //   0.0275);
+    // - in FP64 with two components from 2^23 nodes (256^3 2.63 and 3.07, 192^3
+    //   1.11 and 1.04);
+    // - for one FP32 component on 96-wide columns (96^3 0.0366 and 0.0388).
+    const bool off_lines = (unsigned long long)p.nx * pop_word(p) % 128 != 0;
     K.far_rows = K.far
-                 || (p.lattice == MCLBM_D3Q19 && p.precision != MCLBM_FP16 && p.nx > 64
-                     && (unsigned long long)p.nx * pop_word(p) % 128 != 0) ? 1 : 0;
+                 || (p.lattice == MCLBM_D3Q19
+                     && (((p.precision == MCLBM_FP32 || p.precision == MCLBM_MIXED) && p.nx > 64 && off_lines)
+                         || (p.precision == MCLBM_FP64 && ncomp_of(p.model) == 2 && K.N >= (1LL << 23))
+                         || (p.precision == MCLBM_FP32 && p.model == MCLBM_SC_MP && p.nx % 96 == 0 && p.nx % 64 != 0)))
+                 ? 1 : 0;
     K.enhanced = p.enhanced_eq ? 1 : 0;
     K.conserve = p.model == MCLBM_CG && (p.precision == MCLBM_FP32 || p.precision == MCLBM_MIXED)
                  && p.conserve_mass ? 1 : 0;
@@ -716,6 +725,10 @@ mclbm_status mclbm_create(const mclbm_params *p, void *d_state, size_t bytes, vo
     sim->stream = (hipStream_t)stream;
     sim->fused = p->kernel != MCLBM_KERNEL_TWO_PASS && fused_ok(*p, sim->ops)
                  && (p->kernel == MCLBM_KERNEL_FUSED || auto_prefers_fused(*p));
+    if (p->kernel == MCLBM_KERNEL_AUTO && !sim->fused && p->lattice == MCLBM_D3Q19 && sim->ops->has_fused()) {
+        FusedShape sh;
+        sim->fused = fused_odd_shape(sim->kp, sh, p->precision == MCLBM_FP64);
+    }
     // the two-pass step of a box whose kernel was left to the library runs as
     // one launch over tiles
     sim->tile = p->kernel == MCLBM_KERNEL_AUTO && !sim->fused ? sim->ops->tile_steps(sim->kp) : 0;
@@ -796,7 +809,8 @@ mclbm_status mclbm_fused_tile(const mclbm_sim *sim, int32_t *tx, int32_t *ty, in
         *tz = rows;
     } else {
         FusedShape sh;
-        fused_shape(sim->kp, sh, sim->prm.precision == MCLBM_FP64);
+        const bool wide = sim->prm.precision == MCLBM_FP64;
+        if (!fused_shape(sim->kp, sh, wide)) fused_odd_shape(sim->kp, sh, wide);
         *tx = sh.tx;
         *ty = sh.ty;
         *tz = sh.tz;

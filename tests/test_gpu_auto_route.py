@@ -1,0 +1,68 @@
+"""The automatic kernel choice on D3Q19: one-pass columns with edge columns in
+y where 4 does not divide ny, two-pass kernels where the columns would idle;
+both bitwise equal to the pinned two-pass kernels."""
+import numpy as np
+import pytest
+
+from paper_2110_05197_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2110_05197_amd as M
+    M.lib()
+    return M
+
+
+def fields(M, model, shape):
+    rR, rB = inputs.droplet(shape, min(shape) / 3.0, 1.0, 1.0)
+    return (0.12 + 1.78 * rR, None) if model == "SC_MP" else (rR + 0.02, rB + 0.02)
+
+
+@pytest.mark.parametrize("model", ["CG", "SC_MP", "SC_MC"])
+@pytest.mark.parametrize("precision", ["FP64", "FP32", "MIXED", "FP16"])
+def test_odd_rows_step_in_one_pass(M, model, precision):
+    import torch
+    for box, bc in (((128, 126, 128), (0, 0, 0)), ((187, 131, 190), (1, 1, 2)), ((128, 121, 150), (0, 2, 1))):
+        nx, ny, nz = box
+        kw = dict(lattice=M.D3Q19, model=getattr(M, model), precision=getattr(M, precision), nx=nx, ny=ny, nz=nz, bc=bc)
+        kw.update(dict(G=-5.0, rho0_R=1.9, rho0_B=0.12) if model == "SC_MP" else
+                  dict(A=0.02, tau_R=0.8) if model == "CG" else dict(G_RB=1.2))
+        ini = fields(M, model, (nz, ny, nx))
+        out = []
+        for kernel in (M.KERNEL_AUTO, M.KERNEL_TWO_PASS):
+            print(f"[odd rows] {model} {precision} {box} {bc} kernel={kernel}", flush=True)
+            s = M.Sim(M.make_params(kernel=kernel, **kw))
+            assert s.kernel_used() == (M.KERNEL_TWO_PASS if kernel else M.KERNEL_FUSED)
+            s.init_equilibrium(*ini)
+            assert s.step(5)[0] == M.OK
+            out.append(s.export_f())
+            s.close()
+        assert torch.equal(*out)
+        del out
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("box,precision,kernel", [
+    ((80, 40, 152), "FP32", "TWO_PASS"), ((72, 72, 72), "FP64", "TWO_PASS"), ((100, 100, 100), "FP16", "TWO_PASS"),
+    ((64, 32, 200), "MIXED", "TWO_PASS"), ((128, 128, 128), "FP32", "FUSED"), ((128, 128, 128), "MIXED", "FUSED"),
+    ((176, 176, 176), "FP64", "FUSED"), ((40, 16, 8), "FP32", "FUSED"), ((128, 126, 128), "FP64", "FUSED"),
+    ((150, 101, 90), "FP64", "TWO_PASS")])
+def test_automatic_choice(M, box, precision, kernel):
+    p = M.make_params(lattice=M.D3Q19, precision=getattr(M, precision), nx=box[0], ny=box[1], nz=box[2])
+    s = M.Sim(p)
+    assert s.kernel_used() == getattr(M, "KERNEL_" + kernel)
+    if kernel == "FUSED":
+        tx, ty, tz = s.fused_tile()
+        blocks = -(-box[0] // tx) * -(-box[1] // ty) * -(-box[2] // tz)
+        assert tz >= 1 and blocks >= min(128, box[2])
+    s.close()
+    if box[1] % 4 == 0:   # asked for, the one-pass kernel is there
+        s = M.Sim(dict(p, kernel=M.KERNEL_FUSED))
+        assert s.kernel_used() == M.KERNEL_FUSED
+        s.close()
