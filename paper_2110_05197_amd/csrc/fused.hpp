@@ -140,6 +140,13 @@ constexpr int kLoadSpacing = !YH ? 0 : PR == 1 && MODEL != SC_MC ? 14 : PR == 3 
 // outflow: 0.348 and 0.383, 256^3 1.12 and 1.15.
 template <int PR, bool YH> constexpr bool kPointerLoads = (PR == 1 && !YH) || (PR == 2 && YH);
 
+// The type of a column's node indices.  The mixed-precision columns sit at the
+// register limit (256 a lane in an eight-wave block), and 32-bit indices make
+// their pointer loads hold a zero-extended copy beside each offset: 3-47
+// registers spilled in the periodic kernels that hold 64-bit ones without
+// (2-4 with the mass-keeping collision on ragged rows).
+template <int PR, bool YH> using ColumnIndex = std::conditional_t<PR == 2 && YH, long long, unsigned>;
+
 // One block's work: the TX x TY column at (x0, y0), planes [z0, z1).  An
 // EDGE column is the last one in x when TX does not divide nx: its first
 // w = nx - x0 threads hold nodes, the others only take part in the barriers,
@@ -198,9 +205,10 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
     const int h_slot = (hy + RY) * HX + (hx + 1);
     const int hgx = stencil_coord(x0 + hx, nx, P.bc[0]);
     const int hgy = stencil_coord(y0 + hy, ny, P.bc[1]);
-    const unsigned n_xy = (unsigned)x + (unsigned)nx * (unsigned)y;   // N < 2^31
-    const unsigned h_xy = (unsigned)hgx + (unsigned)nx * (unsigned)hgy;
-    const unsigned sxy = (unsigned)nx * (unsigned)ny;
+    using Idx = ColumnIndex<PR, YH>;   // N < 2^31
+    const Idx n_xy = (Idx)x + (Idx)nx * (Idx)y;
+    const Idx h_xy = (Idx)hgx + (Idx)nx * (Idx)hgy;
+    const Idx sxy = (Idx)nx * (Idx)ny;
     auto ring = [&](int p) { return (p - z0 + 1) & 3; };
 
     bool bad = false;
@@ -216,7 +224,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
             bad = bad || node_bad(r, jv[0] + jv[1] + jv[2]);
         }
     };
-    auto zoff = [&](int p) { return sxy * (unsigned)stencil_coord(p, nz, P.bc[2]); };
+    auto zoff = [&](int p) { return sxy * (Idx)stencil_coord(p, nz, P.bc[2]); };
 
     C c[K][Q];                  // populations of plane z (plane z+1's wait in LDS)
     M drc[2], jc[3], drn[2], jn[3];
@@ -264,7 +272,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
 
         // 2. collide plane z with the stencil values of planes z-1, z, z+1
         if (act) {
-            if constexpr (spacing > 0) dr_.load(src, ahead ? n_xy + zoff(z + 2) : kNoNode);
+            if constexpr (spacing > 0) dr_.load(src, ahead ? (unsigned)(n_xy + zoff(z + 2)) : kNoNode);
             C v[NF][Q];
 #pragma unroll
             for (int i = 1; i < Q; ++i) {
@@ -277,7 +285,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
             for (int a = 0; a < NF; ++a) v[a][0] = C(0);
 
             collide_values<L, MODEL, CONS>(H, c, drc, jc, v, MODEL == SC_MP ? (C)lds[ring(z)][0][my_slot] : C(0));
-            const unsigned n = n_xy + sxy * (unsigned)z;
+            const unsigned n = (unsigned)(n_xy + sxy * (Idx)z);
             // populations that stay on their x (cx = 0) land on whole cache
             // lines and are never read again in this step: stream them past
             // the cache; the x-shifted ones share lines with the neighbouring
