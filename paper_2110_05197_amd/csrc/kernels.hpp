@@ -559,7 +559,15 @@ __device__ __forceinline__ void collide_body(const KParams &P, const void *src, 
     M dr[2], j[3];
     node_moments<L, K>(g, dr, j);
     unsigned nb[L::Q];
-    stencil_nodes<L>(P, x, y, z, nb);
+    if constexpr (PR == 2 && std::is_same_v<MR, MrStaged<FT>>) {
+        // the mixed multirange collide is held to 168 registers: with the
+        // neighbours' coordinates shared it spilled 16 of them off periodic
+        // boxes, direction by direction it fits in 140
+#pragma unroll
+        for (int i = 1; i < L::Q; ++i) nb[i] = (unsigned)stencil_node<L>(P, x, y, z, i);
+    } else {
+        stencil_nodes<L>(P, x, y, z, nb);
+    }
     if constexpr (MODEL == CG) {
         C vR[L::Q], vB[L::Q], vN[L::Q];
         vR[0] = vB[0] = vN[0] = C(0);

@@ -63,3 +63,9 @@ def test_mixed_one_pass_columns(spills):
         seen += 1
         assert n <= (4 if keep == "1" else 0), (name, n)
     assert seen >= 16
+
+
+def test_mixed_multirange_collide(spills):
+    """Near and far addressing, all faces periodic or not: none spilled."""
+    seen = [(n, name) for _, n, name in kernels(spills, r"12k_collide_mrILi2ELb([01])ELb([01])EE")]
+    assert len(seen) == 3 and all(n == 0 for n, _ in seen), seen
