@@ -553,7 +553,7 @@ struct mclbm_sim {
     hipStream_t stream;
     int device;
     bool fused;
-    int tile;          // small D2Q9 box, automatic kernel choice: most steps a tile launch takes (0: none)
+    int tile;          // small D2Q9 box, automatic kernel choice: its tile launches (kTileOne, kTileTwo)
     bool in_batch;
     unsigned *d_flag;
     double *d_partials;
@@ -849,11 +849,11 @@ mclbm_status mclbm_step(mclbm_sim *sim, int64_t nsteps, int64_t check_every, int
         int64_t run = nsteps - done;
         if (check_every > 0) run = std::min(run, check_every - done % check_every);
         for (int64_t t = 0; t < run;) {
-            const int k = sim->tile == 2 && run - t >= 4 ? 4 : 1;
+            const int k = (sim->tile & kTileTwo) && run - t >= 4 ? 4 : 1;
             for (int launch = 0; launch < (k == 4 ? 2 : 1); ++launch) {
                 const void *src = sim->f[sim->cur];
                 void *dst = sim->f[sim->cur ^ 1];
-                if (sim->tile) sim->ops->tile_step(sim->kp, src, dst, sim->d_flag, k == 4 ? 2 : 1, sim->stream);
+                if (k == 4 || (sim->tile & kTileOne)) sim->ops->tile_step(sim->kp, src, dst, sim->d_flag, k == 4 ? 2 : 1, sim->stream);
                 else sim->ops->step(sim->kp, src, dst, sim->field, sim->nfield, sim->d_flag, sim->fused, sim->stream);
                 sim->cur ^= 1;
             }

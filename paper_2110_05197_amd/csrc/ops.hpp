@@ -10,6 +10,9 @@
 
 namespace mclbm {
 
+// Tile launches of one and of two steps that replace the two-pass launches.
+constexpr int kTileOne = 1, kTileTwo = 2;
+
 struct Ops {
     virtual ~Ops() {}
     virtual bool has_fused() const = 0;
@@ -18,8 +21,8 @@ struct Ops {
     // one step: src -> dst (the divergence flag reflects src)
     virtual void step(const KParams &P, const void *src, void *dst, void *field, void *nfield,
                       unsigned *flag, bool fused, hipStream_t s) const = 0;
-    // small-box tile kernels: most steps a launch takes (0: none), and one
-    // launch of `steps` (1 or 2) steps
+    // small-box tile kernels: the launches to take from them (kTileOne,
+    // kTileTwo), and one launch of `steps` (1 or 2) steps
     virtual int tile_steps(const KParams &P) const = 0;
     virtual void tile_step(const KParams &P, const void *src, void *dst, unsigned *flag, int steps,
                            hipStream_t s) const = 0;

@@ -175,11 +175,37 @@ constexpr long long kTile2dSmall = 1 << 15;
 template <int PR> constexpr int kTile2dLarge = PR == 0 ? 16 : 10;
 template <int PR> constexpr long long kTile2dTwoNodes = PR == 0 ? 1 << 18 : 1 << 17;
 
-// Steps per launch of the tile kernels.
+// Thin boxes leave most of a tile's lanes without a node (4 x 44370 FP64 with
+// walls on 64 x 8 tiles: 72.6 us, two-pass launches 18.4).  Lanes per row of
+// TX-wide tiles, over the box (idle rows cost little: 82271 x 2 FP32 8.9 us,
+// two-pass 12.0):
+inline long long tile2d_lanes(const KParams &P, int tx) { return (P.nx + tx - 1LL) / tx * tx * P.ny; }
+// 64 x 8 tiles up to 2.2 lanes per node (nx = 28: 12.0 and 11.7 two-pass; 31:
+// 12.7 and 14.8; 15 and 20 wide boxes 1.06-1.5 times the two-pass time), or
+// where all fit the chip at once (20 x 1888: 5.3 and 7.3).
+inline bool tile2d_wide(const KParams &P)
+{
+    const long long lanes = tile2d_lanes(P, 64);
+    return 5 * lanes <= 11 * P.N || lanes <= 1 << 17;
+}
+// 16 x 4 tiles up to 2^16 lanes (4 x 1041: 5.5 and 7.0; 2 x 10665, 170000
+// lanes, 8.0 and 6.8; 10 x 4885, 78000, 9.9 and 9.0).
+inline bool tile2d_narrow(const KParams &P) { return tile2d_lanes(P, 16) <= 1 << 16; }
+// Two steps: the tiles' nodes, idle ones among them, within a quarter more than
+// the most nodes (6 x 11636: 6.1 and 7.9; 2 x 37184, fivefold: 18.0 and 8.2).
+template <int PR>
+bool tile2d_two(const KParams &P)
+{
+    const int T = P.N <= kTile2dSmall ? 8 : kTile2dLarge<PR>;
+    const long long nodes = tile2d_lanes(P, T) / P.ny * ((P.ny + T - 1LL) / T * T);
+    return P.bc[0] == 0 && P.bc[1] == 0 && P.N <= kTile2dTwoNodes<PR> && 4 * nodes <= 5 * kTile2dTwoNodes<PR>;
+}
+
+// Launches the tile kernels take over from the two passes.
 template <int PR>
 int tile2d_steps(const KParams &P)
 {
-    return P.bc[0] == 0 && P.bc[1] == 0 && P.N <= kTile2dTwoNodes<PR> ? 2 : 1;
+    return (tile2d_wide(P) || tile2d_narrow(P) ? kTileOne : 0) | (tile2d_two<PR>(P) ? kTileTwo : 0);
 }
 
 template <int PR, int MODEL, int T>
@@ -207,7 +233,7 @@ void launch_tile2d(const KParams &P, const void *src, void *dst, unsigned *flag,
         else launch_tile2d_two<PR, MODEL, kTile2dLarge<PR>>(P, src, dst, flag, s);
         return;
     }
-    if (P.N <= kTile2dFew) launch_tile2d_one<PR, MODEL, 16, 4>(P, src, dst, flag, s);
+    if (tile2d_narrow(P) && (P.N <= kTile2dFew || !tile2d_wide(P))) launch_tile2d_one<PR, MODEL, 16, 4>(P, src, dst, flag, s);
     else launch_tile2d_one<PR, MODEL, 64, 8>(P, src, dst, flag, s);
 }
 

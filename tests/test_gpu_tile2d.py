@@ -104,3 +104,35 @@ def test_tile_steps_captured_in_a_graph(M):
             assert np.array_equal(a.export_f().cpu().numpy(), b.export_f().cpu().numpy())
         a.close()
         b.close()
+
+
+THIN = [(2, 37184, 2, (0, 0, 0)), (4, 44370, 0, (0, 1, 0)), (6, 60668, 3, (1, 2, 0)), (8, 53035, 2, (0, 0, 0)),
+        (15, 6380, 2, (0, 1, 0)), (16, 25965, 0, (0, 1, 0)), (20, 16135, 2, (0, 1, 0))]
+NOT_THIN = [(28, 1759, 1, (0, 1, 0)), (40, 8856, 0, (0, 1, 0)), (38709, 2, 2, (0, 1, 0)), (6, 11636, 3, (0, 0, 0))]
+
+
+@pytest.mark.parametrize("nx,ny,prec,bc", THIN + NOT_THIN)
+def test_thin_boxes(M, nx, ny, prec, bc):
+    """Boxes a few nodes wide leave a tile's lanes idle: the two-pass launches'
+    results bit for bit, at no more than 1.25 times their time (tiles whatever
+    the width took 1.3-9 times as long on the first list)."""
+    import torch
+    a = make(M, M.CG, prec, nx, ny, bc, M.KERNEL_AUTO)
+    b = make(M, M.CG, prec, nx, ny, bc, M.KERNEL_TWO_PASS)
+    for n in (1, 6):
+        a.step(n)
+        b.step(n)
+        assert np.array_equal(a.export_f().cpu().numpy(), b.export_f().cpu().numpy())
+    us = ([], [])
+    for _ in range(7):
+        for s, t in zip((a, b), us):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            s.step(80)
+            e[1].record()
+            e[1].synchronize()
+            t.append(e[0].elapsed_time(e[1]) / 80 * 1e3)
+    print(f"[thin] {nx}x{ny} prec={prec} auto {min(us[0]):.1f} two-pass {min(us[1]):.1f} us", flush=True)
+    assert min(us[0]) <= 1.25 * min(us[1])
+    a.close()
+    b.close()
