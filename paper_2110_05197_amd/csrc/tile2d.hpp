@@ -192,13 +192,15 @@ inline bool tile2d_wide(const KParams &P)
 // lanes, 8.0 and 6.8; 10 x 4885, 78000, 9.9 and 9.0).
 inline bool tile2d_narrow(const KParams &P) { return tile2d_lanes(P, 16) <= 1 << 16; }
 // Two steps: the tiles' nodes, idle ones among them, within a quarter more than
-// the most nodes (6 x 11636: 6.1 and 7.9; 2 x 37184, fivefold: 18.0 and 8.2).
+// the most nodes (6 x 11636: 6.1 and 7.9; 2 x 37184, fivefold: 18.0 and 8.2), on
+// 8 x 8 tiles twice as many (2 x 11358: 5.5 and 6.0; 3 x 8620 FP64 9.1 and 7.6).
 template <int PR>
 bool tile2d_two(const KParams &P)
 {
     const int T = P.N <= kTile2dSmall ? 8 : kTile2dLarge<PR>;
     const long long nodes = tile2d_lanes(P, T) / P.ny * ((P.ny + T - 1LL) / T * T);
-    return P.bc[0] == 0 && P.bc[1] == 0 && P.N <= kTile2dTwoNodes<PR> && 4 * nodes <= 5 * kTile2dTwoNodes<PR>;
+    return P.bc[0] == 0 && P.bc[1] == 0 && P.N <= kTile2dTwoNodes<PR>
+           && (T == 8 ? nodes <= 2 * kTile2dSmall : 4 * nodes <= 5 * kTile2dTwoNodes<PR>);
 }
 
 // Launches the tile kernels take over from the two passes.
