@@ -140,12 +140,13 @@ constexpr int kLoadSpacing = !YH ? 0 : PR == 1 && MODEL != SC_MC ? 14 : PR == 3 
 // outflow: 0.348 and 0.383, 256^3 1.12 and 1.15.
 template <int PR, bool YH> constexpr bool kPointerLoads = (PR == 1 && !YH) || (PR == 2 && YH);
 
-// The type of a column's node indices.  The mixed-precision columns sit at the
-// register limit (256 a lane in an eight-wave block), and 32-bit indices make
-// their pointer loads hold a zero-extended copy beside each offset: 3-47
-// registers spilled in the periodic kernels that hold 64-bit ones without
-// (2-4 with the mass-keeping collision on ragged rows).
-template <int PR, bool YH> using ColumnIndex = std::conditional_t<PR == 2 && YH, long long, unsigned>;
+// The type of a column's node indices (N < 2^31).  With 32-bit indices the
+// pointer loads hold a zero-extended copy beside each offset: mixed-precision
+// columns, at the 256 registers an eight-wave block allows, spilled 3-47 of them
+// in the periodic kernels that hold 64-bit ones without (2-4 with the
+// mass-keeping collision on ragged rows), and boxes in the other precisions
+// took 0-3 % longer.
+using ColumnIndex = long long;
 
 // One block's work: the TX x TY column at (x0, y0), planes [z0, z1).  An
 // EDGE column is the last one in x when TX does not divide nx: its first
@@ -205,7 +206,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
     const int h_slot = (hy + RY) * HX + (hx + 1);
     const int hgx = stencil_coord(x0 + hx, nx, P.bc[0]);
     const int hgy = stencil_coord(y0 + hy, ny, P.bc[1]);
-    using Idx = ColumnIndex<PR, YH>;   // N < 2^31
+    using Idx = ColumnIndex;
     const Idx n_xy = (Idx)x + (Idx)nx * (Idx)y;
     const Idx h_xy = (Idx)hgx + (Idx)nx * (Idx)hgy;
     const Idx sxy = (Idx)nx * (Idx)ny;
@@ -557,6 +558,34 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 {
     launch_batch_kinds<PR, MODEL, false>(D, n, fblocks, kinds, s);
     if (kinds >> kFusedFar) launch_batch_kinds<PR, MODEL, true>(D, n, fblocks, kinds, s);
+}
+
+// One-pass kernels that keep 64-bit addressing below the 4 GB line too
+// (KParams::far_rows), from sweeps of 1500 random boxes stepped both ways; t is
+// the time through buffers over the time through pointers (10 % quantile,
+// median, 90 % quantile).
+// - FP16 storage with walls or outflow: t 0.99, 1.02, 1.06 on D3Q19, 1.01, 1.02,
+//   1.06 on D2Q9 (periodic 0.87, 0.95, 1.00 and 0.93, 0.95, 0.98).
+// - D2Q9: mixed colour gradient with walls or outflow, t 1.07, 1.09, 1.11
+//   (periodic 0.94, 0.96, 0.98), and FP32 with two components, t 0.99, 1.005, 1.02,
+//   up to 1.17 (one component 0.99, 0.99, 1.00; FP64 0.96, 0.99, 1.01).
+// - D3Q19 on 96-wide columns, periodic: the Shan-Chen models in FP32, t 1.00, 1.03,
+//   1.05 (every other FP32 box 0.90, 0.97, 1.01, with rows on the cache lines or off
+//   them), the two-component one in FP16 storage too (1.01, 1.04, 1.08).
+// - D3Q19 mixed, with the mass-keeping collision, periodic, more than one column
+//   and rows off the cache lines: t 0.97, 1.01, 1.05 (else 0.95, 0.98, 1.01).
+// - D3Q19 FP64, two components, from 11 * 2^20 nodes: t 0.97, 1.07, 1.15 (8 to
+//   11 * 2^20 nodes 0.95, 0.98, 1.03, fewer 0.90, 0.94, 0.98); not the colour
+//   gradient on ragged rows with walls (0.90, 0.94, 0.96 at any size).
+inline bool column_pointers(const KParams &P, bool flat, int precision, int model)
+{
+    const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
+    const bool wide = P.nx % 96 == 0 && P.nx % 64 != 0;
+    if (precision == 3) return !periodic || (!flat && wide && model == SC_MC);
+    if (flat) return (precision == 1 && model != SC_MP) || (precision == 2 && model == CG && !periodic);
+    if (precision == 1) return model != CG && wide && periodic;
+    if (precision == 2) return P.conserve && periodic && P.nx > 64 && P.nx % 32 != 0;
+    return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
 }
 
 struct FusedShape {

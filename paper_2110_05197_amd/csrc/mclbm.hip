@@ -242,33 +242,10 @@ KParams make_kparams(const mclbm_params &p)
     K.S = pop_stride(p);
     // the step kernels' buffer resources hold byte offsets in 32 bits
     K.far = (unsigned long long)lattice_Q(p.lattice) * (unsigned long long)K.S * pop_word(p) >= (1ull << 32) ? 1 : 0;
-    // One-pass D3Q19 columns keep 64-bit addressing also
-    // - in FP32 and mixed where rows do not start on a cache line each: lines
-    //   are then shared by the rows above and below, and tightly issued buffer
-    //   loads miss what the pointer loads, spaced by their address arithmetic,
-    //   find in L2 (FP32, pointers and buffers, ms per step: 234 x 80 x 119
-    //   colour gradient 0.218 and 0.230, 201 x 160 x 170 0.588 and 0.602; on
-    //   line-aligned rows 160^3 0.357 and 0.331, 192^3 with walls 0.68 and
-    //   0.616).  FP16 storage gains either way (250 x 120 x 101: 0.166 and
-    //   0.155), and so do boxes of one column (27 x 32 x 230 FP32 0.0304 and
-    //   0.0275, 57 x 192 x 239 0.223 and 0.205, but with walls and outflow 0.243
-    //   and 0.251).  Mixed, periodic: 234 x 80 x 120 0.217 and 0.230; with walls
-    //   and outflow 0.250 and 0.246, 100 x 200 x 200 0.507 and 0.480;
-    // - in FP64 with two components from 2^23 nodes (256^3 2.63 and 3.07, 192^3
-    //   1.11 and 1.04);
-    // - for one FP32 component on 96-wide columns (96^3 0.0366 and 0.0388).
-    const bool off_lines = (unsigned long long)p.nx * pop_word(p) % 128 != 0;
-    const bool periodic = p.bc[0] == MCLBM_PERIODIC && p.bc[1] == MCLBM_PERIODIC && p.bc[2] == MCLBM_PERIODIC;
-    K.far_rows = K.far
-                 || (p.lattice == MCLBM_D3Q19
-                     && ((p.precision == MCLBM_FP32 && off_lines && (p.nx > 64 || (K.N >= (1LL << 20) && !periodic)))
-                         || (p.precision == MCLBM_MIXED && off_lines && p.nx > 64 && periodic)
-                         || (p.precision == MCLBM_FP64 && ncomp_of(p.model) == 2 && K.N >= (1LL << 23))
-                         || (p.precision == MCLBM_FP32 && p.model == MCLBM_SC_MP && p.nx % 96 == 0 && p.nx % 64 != 0)))
-                 ? 1 : 0;
     K.enhanced = p.enhanced_eq ? 1 : 0;
     K.conserve = p.model == MCLBM_CG && (p.precision == MCLBM_FP32 || p.precision == MCLBM_MIXED)
                  && p.conserve_mass ? 1 : 0;
+    K.far_rows = K.far || column_pointers(K, p.lattice == MCLBM_D2Q9, p.precision, p.model) ? 1 : 0;
     K.has_outflow = (p.bc[0] == MCLBM_OUTFLOW || p.bc[1] == MCLBM_OUTFLOW || p.bc[2] == MCLBM_OUTFLOW) ? 1 : 0;
     K.rho0[0] = p.rho0_R;
     K.rho0[1] = p.model == MCLBM_SC_MP ? 0.0 : p.rho0_B;

@@ -40,7 +40,7 @@ struct KParams {
     int enhanced;
     int has_outflow;
     int far;             // the arrays of one colour span 4 GB or more: 64-bit addressing
-    int far_rows;        // one-pass kernels with 64-bit addressing: far, or D3Q19 rows off the cache lines
+    int far_rows;        // one-pass kernels with 64-bit addressing: far, or where that is the faster (column_pointers)
     int conserve;        // CG, FP32 / mixed storage: keep each colour's node mass to one rounding
     double rho0[2];      // reference densities of the deviation storage
     double phi[2][3];    // CG: phi_i^k per group; SC: w per group

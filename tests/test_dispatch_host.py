@@ -1,0 +1,70 @@
+"""The launchers' rules (which kernel, which addressing, which columns), compiled
+for the host alone and asked for boxes of every kind; nothing runs on a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FP64, FP32, MIXED, FP16 = range(4)
+CG, SC_MP, SC_MC = range(3)
+PERIODIC, WALLS = (0, 0, 0), (1, 1, 2)
+
+PROGRAM = r"""
+#include <cstdio>
+#include "fused.hpp"
+using namespace mclbm;
+// in: lattice model precision nx ny nz bc0 bc1 bc2 conserve
+int main()
+{
+    int lattice, model, precision;
+    KParams P{};
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d", &lattice, &model, &precision, &P.nx, &P.ny, &P.nz, &P.bc[0],
+                      &P.bc[1], &P.bc[2], &P.conserve) == 10) {
+        P.N = (long long)P.nx * P.ny * P.nz;
+        std::printf("%d\n", (int)column_pointers(P, lattice == 0, precision, model));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """Rows of (lattice, model, precision, (nx, ny, nz), bc, conserve) to rows of answers."""
+    if not shutil.which("hipcc"):
+        pytest.skip("needs hipcc")
+    d = tmp_path_factory.mktemp("dispatch")
+    src, exe = d / "rules.hip", d / "rules"
+    src.write_text(PROGRAM)
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2110_05197_amd", "csrc"),
+                    "-o", str(exe), str(src)], check=True, capture_output=True, text=True)
+
+    def run(rows):
+        text = "".join("%d %d %d %d %d %d %d %d %d %d\n" % (l, m, p, *box, *bc, c) for l, m, p, box, bc, c in rows)
+        out = subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout
+        return [[float(v) for v in line.split()] for line in out.splitlines()]
+    return run
+
+
+def test_addressing_of_the_one_pass_kernels(ask):
+    """Buffer accesses unless the box is one of those that pointers serve better."""
+    near = [(1, CG, FP32, (234, 80, 119), PERIODIC, 0), (1, CG, FP32, (201, 160, 170), PERIODIC, 0),
+            (1, CG, FP32, (57, 192, 239), WALLS, 0), (1, SC_MC, FP32, (110, 136, 217), WALLS, 0),
+            (1, CG, MIXED, (113, 48, 155), PERIODIC, 0), (1, CG, MIXED, (234, 80, 120), WALLS, 1),
+            (1, CG, MIXED, (96, 96, 384), WALLS, 0), (1, CG, FP64, (223, 224, 183), WALLS, 0),
+            (1, CG, FP64, (208, 336, 331), WALLS, 0), (1, CG, FP64, (192, 192, 192), PERIODIC, 0),
+            (1, SC_MP, FP64, (256, 256, 256), PERIODIC, 0), (1, CG, FP16, (160, 160, 160), PERIODIC, 0),
+            (1, SC_MP, FP32, (96, 96, 96), WALLS, 0), (1, CG, FP32, (96, 96, 96), PERIODIC, 0),
+            (0, CG, MIXED, (1900, 1100, 1), PERIODIC, 0), (0, SC_MP, FP32, (1900, 1100, 1), PERIODIC, 0),
+            (0, CG, FP64, (1900, 1100, 1), (0, 1, 0), 0), (0, SC_MC, MIXED, (1900, 1100, 1), (0, 1, 0), 0)]
+    far = [(1, CG, FP16, (96, 72, 90), (0, 1, 0), 0), (1, SC_MC, FP16, (58, 112, 115), WALLS, 0),
+           (1, SC_MP, FP16, (200, 120, 90), WALLS, 0), (1, SC_MC, FP16, (96, 192, 210), PERIODIC, 0),
+           (1, CG, MIXED, (213, 160, 169), PERIODIC, 1), (1, CG, FP64, (256, 256, 256), PERIODIC, 0),
+           (1, SC_MC, FP64, (307, 368, 130), WALLS, 0), (1, CG, FP64, (256, 336, 233), WALLS, 0),
+           (1, SC_MP, FP32, (96, 96, 96), PERIODIC, 0), (1, SC_MC, FP32, (96, 136, 201), PERIODIC, 0),
+           (0, CG, MIXED, (1900, 1100, 1), (0, 1, 0), 0), (0, CG, FP32, (4096, 4096, 1), PERIODIC, 0),
+           (0, CG, FP16, (1900, 1100, 1), (0, 1, 0), 0)]
+    answers = [int(a[0]) for a in ask(near + far)]
+    assert answers == [0] * len(near) + [1] * len(far)
