@@ -670,26 +670,34 @@ inline bool fused_shape(const KParams &P, FusedShape &sh, bool wide = false)
 }
 
 // Automatic choice between the one-pass and the two-pass kernels on D3Q19,
-// where both exist: two-pass where the one-pass shape's overhead (64 x 4
-// columns, half the waves a unit, weighted) is past a line per precision.  FP32
-// colour gradient, one-pass and two-pass us: 80 x 40 x 150 (overhead 2.5) 60.6
-// and 42.1, 72^3 (3.2) 45.4 and 35.9, 100^3 (64 x 4 columns, 2.0) 125 and 88,
-// 64^3 (2.5) 24.7 and 23.0, 128 x 64 x 64 (1.75) 42.8 and 45.3, 144^3 (1.7) 311
-// and 322, 128^3 (1.2) 149 and 205.  FP64 72^3 (2.3) 112 and 65, 48 x 96 x 100
-// (1.85) 84 and 82, 100^3 (1.5) 200 and 210.  Mixed, whose one-pass kernel is
-// the shortest of registers: 64 x 32 x 200 42.6 and 36.6, 128 x 64 x 64 48.1
-// and 47.4, 256 x 64 x 64 (1.4) 86 and 100.  FP16 storage, 64^3 16.1 and 17.7,
-// 100^3 75 and 51.  Boxes of a few thousand nodes take 8-15 us either way.
+// where both exist: two-pass where the one-pass shape's overhead is past a line.
+// The lines come from 1100 random boxes of 24 to 350 nodes a side in every
+// precision and model, a third of them periodic, stepped both ways.  Median
+// one-pass over two-pass time at an overhead of 1.15-1.3, 1.3-1.5 and 2-3:
+//   FP64 CG 0.87, 1.03, 1.45       mixed CG 0.92, 1.02, 1.43
+//   FP32 CG 0.84, 1.07, 1.23       FP32 SC_MP 0.87, 1.11, 1.32
+//   FP32 SC_MC 1.04, 0.9-1.1, 1.32  mixed SC_MP 1.02, 1.12, 1.36
+//   FP16 CG 0.96, 1.03, 1.13       FP16 SC_MP 1.5, 1.5, 1.5
+// and of the mass-keeping collision alike.  64 x 4 columns below FP64 hold half
+// the waves of 64 x 8 ones and break even under 1.3, 96-wide ones at 1.35-1.45 for
+// the colour gradient and 1.2 else.  Of 476 further boxes 17 are left the choice
+// that takes more than 5 % longer, by 37 % at most (FP16 boxes of 10^5 nodes among
+// them, 10 to 20 us either way).  Up to 2^13 nodes a step takes 6-12 us either way.
+inline double one_pass_line(const KParams &P, const FusedShape &sh, int precision, int model)
+{
+    const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
+    const bool low = precision != 0 && sh.tx == 64 && sh.ty == 4;
+    if (precision == 3 ? low || model == SC_MP : low && model == SC_MP) return 1.1;
+    if (low) return 1.25;
+    if (sh.tx == 96) return precision != 3 && model == CG ? 1.47 : 1.2;
+    if (model == SC_MP) return periodic ? 1.35 : 1.25;
+    return periodic ? 1.45 : 1.4;
+}
 inline bool d3_prefers_two_pass(const KParams &P, int precision, int model)
 {
     FusedShape sh;
-    if (!fused_shape(P, sh, precision == 0)) return false;
-    const long long least = precision == 2 ? 1 << 14 : model == SC_MP ? 1 << 18 : 1 << 16;
-    if (P.N < least || P.conserve) return false;
-    const bool low = precision != 0 && sh.tx == 64 && sh.ty == 4;
-    const double weight = !low ? 1.0 : precision == 3 ? 1.8 : 1.35;
-    const double line = precision == 0 ? 1.9 : precision == 2 ? 1.73 : precision == 3 ? 2.6 : 2.0;
-    return weight * fused_overhead(P, sh) > line;
+    if (P.N <= 1 << 13 || !fused_shape(P, sh, precision == 0)) return false;
+    return fused_overhead(P, sh) > one_pass_line(P, sh, precision, model);
 }
 
 // One launch of k_fused; the dynamic-LDS limit is raised once per kernel and
@@ -789,6 +797,15 @@ inline KParams as_marching_2d(const KParams &P)
     Q.bc[1] = 0;
     Q.bc[2] = P.bc[1];
     return Q;
+}
+
+// Automatic choice on D2Q9: rows from 2^19 nodes on (fewer step on tiles), where
+// their segments leave few lanes idle.  One-pass over two-pass time, 160 boxes of
+// 2^19 to 2^21 nodes: up to 128 wide 1.2-70, above 1.5 lanes per node (258 to 340
+// wide) 0.97-1.6, under that 0.7-1.3.
+inline bool rows_preferred(const KParams &P)
+{
+    return P.N >= 1LL << 19 && 2LL * ((P.nx + k2dTX - 1) / k2dTX * k2dTX) <= 3LL * P.nx;
 }
 
 // Row segments and rows per block of the 2-D launch (Q: the box as

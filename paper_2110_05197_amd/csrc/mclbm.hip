@@ -131,13 +131,14 @@ bool fused_ok(const mclbm_params &p, const Ops *ops)
 }
 
 // Automatic kernel choice where both exist: the one-pass kernel, except on
-// D2Q9 boxes under 2^19 nodes, whose few short rows leave the marching kernel
-// latency-bound (they step on tiles instead), and on D3Q19 boxes whose columns
-// would have too much to spare (d3_prefers_two_pass).
+// D2Q9 boxes of fewer than 2^19 nodes, whose few short rows leave the marching
+// kernel latency-bound (they step on tiles instead), or of narrow rows
+// (rows_preferred), and on D3Q19 boxes whose columns would have too much to
+// spare (d3_prefers_two_pass).
 bool auto_prefers_fused(const mclbm_params &p)
 {
-    if (p.lattice == MCLBM_D2Q9) return (long long)p.nx * p.ny >= (1LL << 19);
-    return !d3_prefers_two_pass(make_kparams(p), p.precision, p.model);
+    const KParams K = make_kparams(p);
+    return p.lattice == MCLBM_D2Q9 ? rows_preferred(K) : !d3_prefers_two_pass(K, p.precision, p.model);
 }
 
 // The batched one-pass kernel takes 96 x 4 columns where 96 divides nx and

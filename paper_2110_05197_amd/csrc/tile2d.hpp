@@ -207,6 +207,7 @@ bool tile2d_two(const KParams &P)
 template <int PR>
 int tile2d_steps(const KParams &P)
 {
+    if (P.N >= 1LL << 19) return 0;   // rows, or two-pass launches
     return (tile2d_wide(P) || tile2d_narrow(P) ? kTileOne : 0) | (tile2d_two<PR>(P) ? kTileTwo : 0);
 }
 

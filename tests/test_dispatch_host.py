@@ -23,7 +23,8 @@ int main()
     while (std::scanf("%d %d %d %d %d %d %d %d %d %d", &lattice, &model, &precision, &P.nx, &P.ny, &P.nz, &P.bc[0],
                       &P.bc[1], &P.bc[2], &P.conserve) == 10) {
         P.N = (long long)P.nx * P.ny * P.nz;
-        std::printf("%d\n", (int)column_pointers(P, lattice == 0, precision, model));
+        const bool one = lattice == 0 ? rows_preferred(P) : !d3_prefers_two_pass(P, precision, model);
+        std::printf("%d %d\n", (int)column_pointers(P, lattice == 0, precision, model), (int)one);
     }
 }
 """
@@ -68,3 +69,19 @@ def test_addressing_of_the_one_pass_kernels(ask):
            (0, CG, FP16, (1900, 1100, 1), (0, 1, 0), 0)]
     answers = [int(a[0]) for a in ask(near + far)]
     assert answers == [0] * len(near) + [1] * len(far)
+
+
+def test_automatic_choice_of_the_kernel(ask):
+    """One pass or two, where both exist, on boxes timed with both kernels: (box,
+    one-pass us, two-pass us) on either side of the lines."""
+    one = [((1, CG, FP32, (128, 128, 128), PERIODIC, 0), 133, 195), ((1, CG, FP64, (176, 176, 176), PERIODIC, 0), 950, 1100),
+           ((1, CG, MIXED, (224, 80, 130), PERIODIC, 0), 224, 264), ((1, SC_MC, FP64, (192, 192, 192), PERIODIC, 0), 1, 2),
+           ((1, CG, FP32, (64, 16, 8), PERIODIC, 0), 8, 8), ((0, CG, FP64, (521, 1709, 1), PERIODIC, 0), 69, 77),
+           ((0, SC_MC, FP32, (195417, 22, 1), PERIODIC, 0), 68, 100)]
+    two = [((1, SC_MP, FP16, (194, 136, 98), PERIODIC, 0), 111, 59), ((1, CG, MIXED, (32, 244, 53), (0, 1, 0), 1), 94, 42),
+           ((1, CG, FP32, (32, 172, 101), PERIODIC, 1), 92, 46), ((1, SC_MP, MIXED, (239, 84, 93), WALLS, 0), 128, 85),
+           ((1, SC_MP, FP64, (68, 64, 49), PERIODIC, 0), 31, 20), ((1, SC_MC, FP16, (192, 140, 50), WALLS, 0), 115, 67),
+           ((1, CG, FP64, (27, 12, 199), PERIODIC, 0), 28, 16), ((1, SC_MP, FP32, (90, 176, 97), PERIODIC, 0), 91, 61),
+           ((0, CG, MIXED, (5, 121446, 1), (0, 1, 0), 0), 1029, 32), ((0, CG, FP32, (17, 175932, 1), PERIODIC, 0), 611, 155)]
+    answers = [int(a[1]) for a in ask([c[0] for c in one + two])]
+    assert answers == [1] * len(one) + [0] * len(two)
