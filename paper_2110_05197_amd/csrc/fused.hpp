@@ -10,8 +10,9 @@
 // read and one write of every population per step; no density field is
 // written.  The solo and the batched kernels share the column body.
 //
-// ny % TY == 0; any nx (the last column in x is masked when TX does not
-// divide it) and any nz.
+// Any nx (the last column in x is masked when TX does not divide it), any nz;
+// ny % TY == 0, or, in the columns of their own for such boxes, the last row of
+// columns masked as well.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -588,6 +589,7 @@ inline bool column_pointers(const KParams &P, bool flat, int precision, int mode
     return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
 }
 
+// A box's columns (D3Q19) on the one-pass kernel, planned once per simulation.
 struct FusedShape {
     int tx, ty, tz;
     bool ragged;   // the last column in x is an edge column
@@ -608,41 +610,33 @@ inline double fused_overhead(const KParams &P, const FusedShape &sh)
 
 // z-chunks: at most one block per compute unit -- more resident blocks per XCD
 // overflow its L2 and the halo re-reads miss, and a grid just above 256 blocks
-// runs a second, nearly empty round.  Where that leaves too many units idle,
-// the chunk length with the least rounds * (planes + 3) instead: FP64 176^3,
-// 132 columns, 1.34 -> 0.95 ms, 192^3 1.43 -> 1.04, 200^3 (200 blocks) 1.66 ->
-// 1.48; FP32 gains less from filling up (176^3, 198 blocks, 0.549 -> 0.520)
-// and loses from 200 blocks on (200^3 0.860 -> 0.916).
-inline void fused_chunks(const KParams &P, FusedShape &sh, bool wide)
+// runs a second, nearly empty round.  Where that leaves units idle, the chunk
+// length with the least rounds * (planes + 3) instead, if that promises a tenth
+// less than one round: 170 boxes of 130 to 232 blocks in one round, both ways,
+// promised 0.66-0.9, took 0.72-1.0 of the time (median 0.86; 247 x 192 x 201 FP64
+// 1.04), promised more, 0.84-1.22 (median 0.99).  FP32 boxes of 200 blocks and more
+// gain nothing at 0.83-0.91 either (200^3 1.05, 309 x 160 x 193 1.12, 262 x 320 x 112
+// 0.91), FP16 storage gains what is promised (median 0.92 at 0.79-0.98).
+inline void fused_chunks(const KParams &P, FusedShape &sh, int precision)
 {
     const long long txy = (long long)((P.nx + sh.tx - 1) / sh.tx) * ((P.ny + sh.ty - 1) / sh.ty);
     const long long tiles_z = std::max<long long>(1, 256 / txy);
     sh.tz = (int)((P.nz + tiles_z - 1) / tiles_z);
-    const long long blocks = txy * ((P.nz + sh.tz - 1) / sh.tz);
-    if (blocks >= (wide ? 204 : 199) || txy * P.nz < 256) return;
-    long long best = -1;
-    for (int chunks = 1; chunks <= P.nz; ++chunks) {
-        const int tz = (P.nz + chunks - 1) / chunks;
-        const long long rounds = (txy * ((P.nz + tz - 1) / tz) + 255) / 256;
-        if (best < 0 || rounds * (tz + 3) < best) {
-            best = rounds * (tz + 3);
-            sh.tz = tz;
+    const long long blocks = txy * ((P.nz + sh.tz - 1) / sh.tz), plain = sh.tz + 3;
+    if (blocks >= (precision == 1 ? 200 : 256) || txy * P.nz < 256) return;
+    // the most chunks of every number of rounds, until the planes that the
+    // columns cannot do without leave no less cost (about sqrt(nz) steps)
+    long long best = plain, tz = sh.tz;
+    for (long long rounds = 1; 256 * (best - 3 * rounds) > txy * P.nz; ++rounds) {
+        const long long chunks = std::min<long long>(P.nz, 256 * rounds / txy), t = (P.nz + chunks - 1) / chunks;
+        const long long cost = (txy * ((P.nz + t - 1) / t) + 255) / 256 * (t + 3);
+        if (cost < best) {
+            best = cost;
+            tz = t;
         }
+        if (chunks == P.nz) break;
     }
-}
-
-// The automatic choice for D3Q19 boxes whose ny 4 does not divide: one-pass
-// columns with edge columns in y too where they have little to spare (128 x 126
-// x 128, overhead 1.2: FP32 0.212 -> 0.161 ms, FP64 0.418 -> 0.302; 190 x 57 x
-// 120, 1.5: 0.136 and 0.133).
-inline bool fused_odd_shape(const KParams &P, FusedShape &sh, bool wide)
-{
-    sh.tx = 64;
-    sh.ty = wide ? 4 : 8;
-    sh.ragged = true;
-    sh.odd = true;
-    fused_chunks(P, sh, wide);
-    return P.ny % 4 != 0 && !P.far && !P.conserve && P.N >= (1 << 18) && fused_overhead(P, sh) < 1.3;
+    if (precision == 3 || 10 * best <= 9 * plain) sh.tz = (int)tz;
 }
 
 // Tile choice: 64-wide rows (narrower rows split the x-shifted pushes' cache
@@ -653,8 +647,9 @@ inline bool fused_odd_shape(const KParams &P, FusedShape &sh, bool wide)
 // FP32 size.  Where 96 divides nx and 64 does not (nx = 96, 288, ...), the
 // columns are 96 x 4 instead (six waves, no lane idle), in place of 64-wide
 // columns whose last one would leave a third of its lanes or more idle.
-inline bool fused_shape(const KParams &P, FusedShape &sh, bool wide = false)
+inline bool fused_shape(const KParams &P, FusedShape &sh, int precision)
 {
+    const bool wide = precision == 0;
     sh.tx = 64;
     sh.ragged = P.nx % 64 != 0;
     if (!wide && P.nx % 96 == 0 && P.nx % 64 != 0 && P.ny % 4 == 0) {
@@ -665,7 +660,7 @@ inline bool fused_shape(const KParams &P, FusedShape &sh, bool wide = false)
     else if (P.ny % 4 == 0) sh.ty = 4;
     else return false;
     sh.odd = false;
-    fused_chunks(P, sh, wide);
+    fused_chunks(P, sh, precision);
     return true;
 }
 
@@ -696,8 +691,24 @@ inline double one_pass_line(const KParams &P, const FusedShape &sh, int precisio
 inline bool d3_prefers_two_pass(const KParams &P, int precision, int model)
 {
     FusedShape sh;
-    if (P.N <= 1 << 13 || !fused_shape(P, sh, precision == 0)) return false;
+    if (P.N <= 1 << 13 || !fused_shape(P, sh, precision)) return false;
     return fused_overhead(P, sh) > one_pass_line(P, sh, precision, model);
+}
+
+// The automatic choice for D3Q19 boxes whose ny 4 does not divide: one-pass
+// columns with edge columns in y too where they have little to spare (128 x 126
+// x 128, overhead 1.2: FP32 0.212 -> 0.161 ms, FP64 0.418 -> 0.302; 40 random boxes
+// under 1.3: 0.75-1.03 of the two-pass time; FP16 storage 0.81-1.11, its one
+// multiphase box 1.4).
+constexpr int odd_column_height(bool wide) { return wide ? 4 : 8; }
+inline bool fused_odd_shape(const KParams &P, FusedShape &sh, int precision)
+{
+    sh.tx = 64;
+    sh.ty = odd_column_height(precision == 0);
+    sh.ragged = true;
+    sh.odd = true;
+    fused_chunks(P, sh, precision);
+    return P.ny % 4 != 0 && !P.far && !P.conserve && P.N >= (1 << 18) && fused_overhead(P, sh) < 1.3;
 }
 
 // One launch of k_fused; the dynamic-LDS limit is raised once per kernel and
@@ -768,17 +779,14 @@ void launch_fused_cols(const KParams &P, const FusedShape &sh, const void *src, 
 }
 
 template <int PR, int MODEL>
-void launch_fused(const KParams &P, const void *src, void *dst, unsigned *flag, hipStream_t s)
+void launch_fused(const KParams &P, const FusedShape &sh, const void *src, void *dst, unsigned *flag, hipStream_t s)
 {
-    FusedShape sh;
-    if (!fused_shape(P, sh, PR == 0)) fused_odd_shape(P, sh, PR == 0);  // checked at create time
     if constexpr (PR != 0) {
         if (sh.tx == 96) {
             launch_fused_shape<PR, MODEL, 96, 4, kColsFull>(P, src, dst, flag, sh.tz, s);
             return;
         }
     }
-    // (one column height per precision for odd boxes)
     if (sh.ty == 4) launch_fused_cols<PR, MODEL, 4>(P, sh, src, dst, flag, s);
     else if constexpr (PR != 0) launch_fused_cols<PR, MODEL, 8>(P, sh, src, dst, flag, s);
 }

@@ -127,7 +127,7 @@ bool fused_ok(const mclbm_params &p, const Ops *ops)
     // fused kernel does not hold them
     if (!ops || !ops->has_fused() || multirange_of(p)) return false;
     if (p.lattice == MCLBM_D2Q9) return true;   // rows of any length, any ny
-    return fused_shape(make_kparams(p), sh, p.precision == MCLBM_FP64);
+    return fused_shape(make_kparams(p), sh, p.precision);
 }
 
 // Automatic kernel choice where both exist: the one-pass kernel, except on
@@ -531,6 +531,7 @@ struct mclbm_sim {
     hipStream_t stream;
     int device;
     bool fused;
+    FusedShape shape;  // of the one-pass kernel, where D3Q19 has one
     int tile;          // small D2Q9 box, automatic kernel choice: its tile launches (kTileOne, kTileTwo)
     bool in_batch;
     unsigned *d_flag;
@@ -708,9 +709,11 @@ mclbm_status mclbm_create(const mclbm_params *p, void *d_state, size_t bytes, vo
     sim->stream = (hipStream_t)stream;
     sim->fused = p->kernel != MCLBM_KERNEL_TWO_PASS && fused_ok(*p, sim->ops)
                  && (p->kernel == MCLBM_KERNEL_FUSED || auto_prefers_fused(*p));
-    if (p->kernel == MCLBM_KERNEL_AUTO && !sim->fused && p->lattice == MCLBM_D3Q19 && sim->ops->has_fused()) {
-        FusedShape sh;
-        sim->fused = fused_odd_shape(sim->kp, sh, p->precision == MCLBM_FP64);
+    if (p->lattice == MCLBM_D3Q19 && sim->ops->has_fused()) {
+        if (!fused_shape(sim->kp, sim->shape, p->precision)) {
+            const bool odd = fused_odd_shape(sim->kp, sim->shape, p->precision);
+            sim->fused = p->kernel == MCLBM_KERNEL_AUTO && odd;
+        }
     }
     // the two-pass step of a box whose kernel was left to the library runs as
     // one launch over tiles
@@ -791,12 +794,9 @@ mclbm_status mclbm_fused_tile(const mclbm_sim *sim, int32_t *tx, int32_t *ty, in
         *ty = 1;
         *tz = rows;
     } else {
-        FusedShape sh;
-        const bool wide = sim->prm.precision == MCLBM_FP64;
-        if (!fused_shape(sim->kp, sh, wide)) fused_odd_shape(sim->kp, sh, wide);
-        *tx = sh.tx;
-        *ty = sh.ty;
-        *tz = sh.tz;
+        *tx = sim->shape.tx;
+        *ty = sim->shape.ty;
+        *tz = sim->shape.tz;
     }
     return MCLBM_OK;
 }
@@ -819,6 +819,7 @@ mclbm_status mclbm_step(mclbm_sim *sim, int64_t nsteps, int64_t check_every, int
     mclbm_status s = check_sim(sim);
     if (s) return s;
     if (nsteps < 0 || check_every < 0) return fail(MCLBM_EINVAL, "negative step count");
+    const FusedShape *one_pass = sim->fused ? &sim->shape : nullptr;
     int64_t done = 0;
     while (done < nsteps) {
         // steps up to the next check.  Launches of two steps go in pairs, so
@@ -832,7 +833,7 @@ mclbm_status mclbm_step(mclbm_sim *sim, int64_t nsteps, int64_t check_every, int
                 const void *src = sim->f[sim->cur];
                 void *dst = sim->f[sim->cur ^ 1];
                 if (k == 4 || (sim->tile & kTileOne)) sim->ops->tile_step(sim->kp, src, dst, sim->d_flag, k == 4 ? 2 : 1, sim->stream);
-                else sim->ops->step(sim->kp, src, dst, sim->field, sim->nfield, sim->d_flag, sim->fused, sim->stream);
+                else sim->ops->step(sim->kp, src, dst, sim->field, sim->nfield, sim->d_flag, one_pass, sim->stream);
                 sim->cur ^= 1;
             }
             t += k;

@@ -10,6 +10,8 @@
 
 namespace mclbm {
 
+struct FusedShape;   // fused.hpp
+
 // Tile launches of one and of two steps that replace the two-pass launches.
 constexpr int kTileOne = 1, kTileTwo = 2;
 
@@ -18,9 +20,10 @@ struct Ops {
     virtual bool has_fused() const = 0;
     // blocks of the batched one-pass kernel the device holds at once (0: none)
     virtual long long batch_fused_resident() const = 0;
-    // one step: src -> dst (the divergence flag reflects src)
+    // one step: src -> dst (the divergence flag reflects src); one_pass: the
+    // one-pass kernel's columns (D2Q9: any), null for the two-pass kernels
     virtual void step(const KParams &P, const void *src, void *dst, void *field, void *nfield,
-                      unsigned *flag, bool fused, hipStream_t s) const = 0;
+                      unsigned *flag, const FusedShape *one_pass, hipStream_t s) const = 0;
     // small-box tile kernels: the launches to take from them (kTileOne,
     // kTileTwo), and one launch of `steps` (1 or 2) steps
     virtual int tile_steps(const KParams &P) const = 0;
@@ -80,7 +83,7 @@ template <class L, int PR, int MODEL, bool REP> constexpr bool batch_fused_avail
     return fused_available<L, PR, MODEL, REP>() && L::Q == 19;
 }
 template <int PR, int MODEL>
-void launch_fused(const KParams &P, const void *src, void *dst, unsigned *flag, hipStream_t s);
+void launch_fused(const KParams &P, const FusedShape &sh, const void *src, void *dst, unsigned *flag, hipStream_t s);
 template <int PR, int MODEL>
 void launch_fused2d(const KParams &P, const void *src, void *dst, unsigned *flag, hipStream_t s);
 template <int PR>
@@ -105,12 +108,12 @@ struct OpsT final : Ops {
     }
 
     void step(const KParams &P, const void *src, void *dst, void *field, void *nfield, unsigned *flag,
-              bool fused, hipStream_t s) const override
+              const FusedShape *one_pass, hipStream_t s) const override
     {
         bool done = false;
         if constexpr (fused_available<L, PR, MODEL, REP>()) {
-            if (fused) {
-                if constexpr (L::Q == 19) launch_fused<PR, MODEL>(P, src, dst, flag, s);
+            if (one_pass) {
+                if constexpr (L::Q == 19) launch_fused<PR, MODEL>(P, *one_pass, src, dst, flag, s);
                 else launch_fused2d<PR, MODEL>(P, src, dst, flag, s);
                 done = true;
             }

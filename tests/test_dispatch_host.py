@@ -24,7 +24,10 @@ int main()
                       &P.bc[1], &P.bc[2], &P.conserve) == 10) {
         P.N = (long long)P.nx * P.ny * P.nz;
         const bool one = lattice == 0 ? rows_preferred(P) : !d3_prefers_two_pass(P, precision, model);
-        std::printf("%d %d\n", (int)column_pointers(P, lattice == 0, precision, model), (int)one);
+        FusedShape sh{};
+        if (lattice == 1 && !fused_shape(P, sh, precision)) fused_odd_shape(P, sh, precision);
+        std::printf("%d %d %d %d %d\n", (int)column_pointers(P, lattice == 0, precision, model), (int)one, sh.tx, sh.ty,
+                    sh.tz);
     }
 }
 """
@@ -85,3 +88,36 @@ def test_automatic_choice_of_the_kernel(ask):
            ((0, CG, MIXED, (5, 121446, 1), (0, 1, 0), 0), 1029, 32), ((0, CG, FP32, (17, 175932, 1), PERIODIC, 0), 611, 155)]
     answers = [int(a[1]) for a in ask([c[0] for c in one + two])]
     assert answers == [1] * len(one) + [0] * len(two)
+
+
+def test_march_lengths_are_the_best_of_all(ask):
+    """The planes of a chunk, found in about sqrt(nz) steps, against every number
+    of chunks: the least rounds * (planes + 3) of 256 blocks a round, fewest chunks
+    on a tie, where that is a tenth less than one round's."""
+    import random
+    import time
+    rng = random.Random(5)
+    rows = []
+    for _ in range(1500):
+        box = (rng.randint(2, 500), rng.randint(2, 500), rng.choice([rng.randint(2, 60), rng.randint(60, 3000)]))
+        rows.append((1, rng.randint(0, 2), rng.randint(0, 3), box, PERIODIC, 0))
+    searched = 0
+    for (_, _, prec, (nx, ny, nz), _, _), (_, _, tx, ty, tz) in zip(rows, ask(rows)):
+        columns = -(-nx // int(tx)) * -(-ny // int(ty))
+        plain = -(-nz // max(1, 256 // columns))
+        blocks = columns * -(-nz // plain)
+        best, want = plain + 3, plain
+        if blocks < (200 if prec == FP32 else 256) and columns * nz >= 256:
+            for chunks in range(1, nz + 1):
+                t = -(-nz // chunks)
+                cost = -(-columns * -(-nz // t) // 256) * (t + 3)
+                if cost < best:
+                    best, want = cost, t
+            if prec != FP16 and 10 * best > 9 * (plain + 3):
+                want = plain
+        searched += want != plain
+        assert tz == want, (nx, ny, nz, prec, tz, want)
+    assert searched > 100
+    start = time.perf_counter()
+    ask([(1, CG, FP32, (2, 4, 260000000), PERIODIC, 0)] * 20)   # a search over nz took seconds a box
+    assert time.perf_counter() - start < 2
