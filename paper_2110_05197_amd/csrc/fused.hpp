@@ -766,13 +766,15 @@ template <int PR, int MODEL, int TY>
 void launch_fused_cols(const KParams &P, const FusedShape &sh, const void *src, void *dst, unsigned *flag, hipStream_t s)
 {
     if (sh.odd) {
-        const int tiles_x = (P.nx + 63) / 64, tiles_y = (P.ny + TY - 1) / TY;
-        if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0)
-            launch_fused_one<PR, MODEL, 64, TY, true, kColsOdd, D3Q19, D3Q19, false, false>(P, src, dst, flag, sh.tz,
-                                                                                           tiles_x, tiles_y, s);
-        else
-            launch_fused_one<PR, MODEL, 64, TY, false, kColsOdd, D3Q19, D3Q19, false, false>(P, src, dst, flag, sh.tz,
-                                                                                            tiles_x, tiles_y, s);
+        if constexpr (TY == odd_column_height(PR == 0)) {
+            const int tiles_x = (P.nx + 63) / 64, tiles_y = (P.ny + TY - 1) / TY;
+            if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0)
+                launch_fused_one<PR, MODEL, 64, TY, true, kColsOdd, D3Q19, D3Q19, false, false>(
+                    P, src, dst, flag, sh.tz, tiles_x, tiles_y, s);
+            else
+                launch_fused_one<PR, MODEL, 64, TY, false, kColsOdd, D3Q19, D3Q19, false, false>(
+                    P, src, dst, flag, sh.tz, tiles_x, tiles_y, s);
+        }
     } else if (!sh.ragged) launch_fused_shape<PR, MODEL, 64, TY, kColsFull>(P, src, dst, flag, sh.tz, s);
     else if (P.nx > 64) launch_fused_shape<PR, MODEL, 64, TY, kColsRagged>(P, src, dst, flag, sh.tz, s);
     else launch_fused_shape<PR, MODEL, 64, TY, kColsNarrow>(P, src, dst, flag, sh.tz, s);
