@@ -94,7 +94,8 @@ typedef int32_t mclbm_status;
 /* Kernel choice for mclbm_step. */
 #define MCLBM_KERNEL_AUTO 0     /* the faster: D3Q19 one pass, or two passes where */
                                 /* its columns would idle; D2Q9 one pass from 2^19 */
-                                /* nodes, below both passes in a launch over tiles */
+                                /* nodes (not narrow rows), below both passes in a */
+                                /* launch over tiles (not thin boxes)              */
 #define MCLBM_KERNEL_TWO_PASS 1 /* density-field pass + collide/stream pass       */
 #define MCLBM_KERNEL_FUSED 2    /* one pass per step: CG/SC without repulsion     */
 
@@ -322,8 +323,10 @@ mclbm_status mclbm_kernel_used(const mclbm_sim *sim, int32_t *kernel);
 /* Work of one block of the one-pass kernel: a *tx x *ty column of nodes
  * marching through *tz planes (D3Q19), or a row segment of *tx nodes marching
  * through *tz rows (D2Q9, *ty = 1); blocks at the end of the lattice march
- * fewer.  Host only; EUNSUPPORTED when the simulation runs the two-pass
- * kernels, EINVAL on NULL. */
+ * fewer.  Where the automatic choice took the two-pass kernels over a one-pass
+ * kernel (D3Q19 with ny % 4 == 0, D2Q9 from 2^19 nodes), that kernel's blocks.
+ * Host only; EUNSUPPORTED when there is no one-pass kernel to choose or the
+ * two-pass kernels were asked for, EINVAL on NULL. */
 mclbm_status mclbm_fused_tile(const mclbm_sim *sim, int32_t *tx, int32_t *ty, int32_t *tz);
 
 /* ------------------------------------------------------------------------ */

@@ -786,8 +786,13 @@ mclbm_status mclbm_kernel_used(const mclbm_sim *sim, int32_t *kernel)
 mclbm_status mclbm_fused_tile(const mclbm_sim *sim, int32_t *tx, int32_t *ty, int32_t *tz)
 {
     if (!sim || !tx || !ty || !tz) return fail(MCLBM_EINVAL, "null argument");
-    if (!sim->fused) return fail(MCLBM_EUNSUPPORTED, "the simulation runs the two-pass kernels");
-    if (sim->prm.lattice == MCLBM_D2Q9) {
+    // left to the automatic choice, a box that has a one-pass kernel is told its
+    // columns whichever kernel was taken (D2Q9: from 2^19 nodes)
+    const bool flat = sim->prm.lattice == MCLBM_D2Q9;
+    const bool either = sim->prm.kernel == MCLBM_KERNEL_AUTO && sim->ops->has_fused()
+                        && (flat ? sim->kp.N >= 1LL << 19 : !sim->shape.odd);
+    if (!sim->fused && !either) return fail(MCLBM_EUNSUPPORTED, "the simulation runs the two-pass kernels");
+    if (flat) {
         int tiles_x = 0, rows = 0;
         fused2d_rows(as_marching_2d(sim->kp), tiles_x, rows);
         *tx = k2dTX;

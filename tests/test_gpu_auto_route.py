@@ -66,3 +66,28 @@ def test_automatic_choice(M, box, precision, kernel):
         s = M.Sim(dict(p, kernel=M.KERNEL_FUSED))
         assert s.kernel_used() == M.KERNEL_FUSED
         s.close()
+
+
+@pytest.mark.parametrize("lattice,precision,box,answers", [
+    ("D3Q19", "FP32", (64, 64, 64), True), ("D3Q19", "FP64", (72, 72, 72), True), ("D3Q19", "MIXED", (32, 244, 53), True),
+    ("D2Q9", "FP32", (17, 40000, 1), True), ("D3Q19", "FP64", (150, 101, 90), False), ("D2Q9", "FP32", (512, 512, 1), False)])
+def test_columns_of_a_box_left_to_the_automatic_choice(M, lattice, precision, box, answers):
+    """mclbm_fused_tile answers for every box whose one-pass kernel was there to
+    choose, as for the one-pass kernel asked for, also where two passes are
+    taken; pinned to the two-pass kernels it refuses."""
+    nx, ny, nz = box
+    kw = dict(lattice=getattr(M, lattice), precision=getattr(M, precision), nx=nx, ny=ny, nz=nz)
+    s = M.Sim(M.make_params(**kw))
+    assert s.kernel_used() == M.KERNEL_TWO_PASS
+    if answers:
+        one = M.Sim(M.make_params(kernel=M.KERNEL_FUSED, **kw))
+        assert s.fused_tile() == one.fused_tile()
+        one.close()
+        two = M.Sim(M.make_params(kernel=M.KERNEL_TWO_PASS, **kw))
+        with pytest.raises(M.MclbmError):
+            two.fused_tile()
+        two.close()
+    else:
+        with pytest.raises(M.MclbmError):
+            s.fused_tile()
+    s.close()
