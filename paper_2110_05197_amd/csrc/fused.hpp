@@ -492,38 +492,39 @@ inline int batch_group_tz(const long long *cols, const int *nz, int n, long long
     return best;
 }
 
+// Blocks a compute unit holds of the batched one-pass kernels of one column
+// width: the fewest over periodic or not, edge columns or not, near and FAR.
+template <int PR, int MODEL, bool WIDE>
+int batch_fused_per_cu()
+{
+    constexpr int lds = fused_lds_bytes<PR, MODEL, kb_tx(WIDE), kb_ty(PR, WIDE)>();
+    constexpr bool EDGE = !WIDE;
+    const void *fns[8] = {
+        (const void *)kb_fused<PR, MODEL, true, false, WIDE, false>, (const void *)kb_fused<PR, MODEL, false, false, WIDE, false>,
+        (const void *)kb_fused<PR, MODEL, true, false, WIDE, true>, (const void *)kb_fused<PR, MODEL, false, false, WIDE, true>,
+        (const void *)kb_fused<PR, MODEL, true, EDGE, WIDE, false>, (const void *)kb_fused<PR, MODEL, false, EDGE, WIDE, false>,
+        (const void *)kb_fused<PR, MODEL, true, EDGE, WIDE, true>, (const void *)kb_fused<PR, MODEL, false, EDGE, WIDE, true>};
+    int per_cu = 1 << 30;
+    for (int i = 0; i < (EDGE ? 8 : 4); ++i) {
+        int b = 0;
+        (void)hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fns[i], kb_tx(WIDE) * kb_ty(PR, WIDE), lds) != hipSuccess) return 0;
+        per_cu = std::min(per_cu, b);
+    }
+    return std::max(1, per_cu);
+}
+
 // Blocks of kb_fused<PR, MODEL, ...> the device holds at once (the smallest
 // over the kinds).
 template <int PR, int MODEL>
 long long batch_fused_resident()
 {
-    constexpr int lds = fused_lds_bytes<PR, MODEL, kBatchTX, batch_ty(PR)>();
-    int dev = 0, cus = 0, per_cu = 1 << 30;
-    if (hipGetDevice(&dev) != hipSuccess
+    int dev = 0, cus = 0, per_cu = batch_fused_per_cu<PR, MODEL, false>();
+    if constexpr (batch_wide_kernel(PR, MODEL)) per_cu = std::min(per_cu, batch_fused_per_cu<PR, MODEL, true>());
+    if (per_cu == 0 || hipGetDevice(&dev) != hipSuccess
         || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 256;
-    const void *fns[4] = {(const void *)kb_fused<PR, MODEL, true, false>, (const void *)kb_fused<PR, MODEL, false, false>,
-                          (const void *)kb_fused<PR, MODEL, true, true>, (const void *)kb_fused<PR, MODEL, false, true>};
-    for (const void *fn : fns) {
-        int b = 0;
-        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fn, kBatchTX * batch_ty(PR), lds) != hipSuccess)
-            return 256;
-        per_cu = std::min(per_cu, b);
-    }
-    if constexpr (batch_wide_kernel(PR, MODEL)) {
-        constexpr int lds_w = fused_lds_bytes<PR, MODEL, kBatchWideTX, kBatchWideTY>();
-        const void *wide[2] = {(const void *)kb_fused<PR, MODEL, true, false, true>,
-                               (const void *)kb_fused<PR, MODEL, false, false, true>};
-        for (const void *fn : wide) {
-            int b = 0;
-            (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_w);
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fn, kBatchWideTX * kBatchWideTY, lds_w) != hipSuccess)
-                return 256;
-            per_cu = std::min(per_cu, b);
-        }
-    }
-    return (long long)std::max(1, per_cu) * std::max(1, cus);
+    return (long long)per_cu * std::max(1, cus);
 }
 
 // kinds: the fused_kind() bits of the simulations present.  Every launch
