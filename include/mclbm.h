@@ -355,7 +355,9 @@ mclbm_status mclbm_fused_tile(const mclbm_sim *sim, int32_t *tx, int32_t *ty, in
  * where 96 divides nx and 64 does not, except in FP64 and for the mixed
  * colour gradient; z-chunks sized for the group; one launch per kind present
  * in the group: all faces periodic or not, nx a multiple of 64 or not, 96-wide
- * columns or not); the others in batched two-pass launches.  The
+ * columns or not); the others in batched two-pass launches, among them, left to
+ * the automatic choice, those of 2^16 nodes up that the two-pass launches step
+ * faster (most in mixed precision and FP16 storage, some with walls).  The
  * per-node arithmetic is the same as mclbm_step's, so a sim's result is
  * bitwise the same alone (either kernel) and in any batch. */
 mclbm_status mclbm_batch_create(mclbm_sim *const *sims, int32_t n, const int64_t *target_steps,

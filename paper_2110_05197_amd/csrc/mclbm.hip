@@ -141,6 +141,28 @@ bool auto_prefers_fused(const mclbm_params &p)
     return p.lattice == MCLBM_D2Q9 ? rows_preferred(K) : !d3_prefers_two_pass(K, p.precision, p.model);
 }
 
+// Batches left to the automatic choice, boxes of 2^16 nodes up (FP64: 2^17):
+// classes whose batched one-pass step is the slower.  One-pass over two-pass time
+// of batches of 1-8 equal boxes, 700 of them (least, median, most): mixed CG 0.98,
+// 1.3, 1.8, SC_MP with walls or wider than 96 1.1, 1.35, 1.7 (else 0.83-1.18), SC_MC
+// likewise 0.98, 1.3, 1.6 (else 0.85-1.2, on 96-wide columns 0.71-0.87); FP16 SC_MP
+// 0.93, 1.4, 1.8, SC_MC 0.93, 1.15, 1.4 (64 wide, periodic, 0.97-1.03), CG with walls
+// 1.03, 1.15, 1.3; with walls also FP32 SC_MP 1.02, 1.2, 1.4 and FP64 CG 1.04, 1.1,
+// 1.3.  The others 0.68-1.37, median 0.98.
+bool batch_two_pass_faster(const mclbm_params &p)
+{
+    const long long least = p.precision == MCLBM_FP64 ? 1 << 17 : 1 << 16;
+    if (p.kernel != MCLBM_KERNEL_AUTO || (long long)p.nx * p.ny * p.nz < least) return false;
+    const bool periodic = p.bc[0] == MCLBM_PERIODIC && p.bc[1] == MCLBM_PERIODIC && p.bc[2] == MCLBM_PERIODIC;
+    const bool wide = batch_wide(p.precision, p.model, p.nx, p.ny);
+    switch (p.precision) {
+    case MCLBM_MIXED: return p.model == MCLBM_CG || ((!periodic || p.nx > 96) && !(p.model == MCLBM_SC_MC && wide));
+    case MCLBM_FP16: return p.model == MCLBM_SC_MP || !periodic || (p.model == MCLBM_SC_MC && p.nx != 64);
+    case MCLBM_FP32: return p.model == MCLBM_SC_MP && !periodic;
+    default: return p.model == MCLBM_CG && !periodic;
+    }
+}
+
 // The batched one-pass kernel takes 96 x 4 columns where 96 divides nx and
 // 64 does not (batch_wide), else 64 x batch_ty columns, the last one in x
 // masked when 64 does not divide nx, as long as at least three quarters of
@@ -152,7 +174,7 @@ bool auto_prefers_fused(const mclbm_params &p)
 // one-pass kernel for this lattice, model and precision).
 bool batch_fused_ok(const mclbm_params &p, long long resident)
 {
-    if (resident <= 0 || multirange_of(p) || p.kernel == MCLBM_KERNEL_TWO_PASS) return false;
+    if (resident <= 0 || multirange_of(p) || p.kernel == MCLBM_KERNEL_TWO_PASS || batch_two_pass_faster(p)) return false;
     if (batch_wide(p.precision, p.model, p.nx, p.ny)) return true;
     const long long lanes = (long long)kBatchTX * ((p.nx + kBatchTX - 1) / kBatchTX);
     return p.ny % batch_ty(p.precision) == 0 && 4LL * p.nx >= 3 * lanes;
