@@ -559,10 +559,12 @@ __device__ __forceinline__ void collide_body(const KParams &P, const void *src, 
     M dr[2], j[3];
     node_moments<L, K>(g, dr, j);
     unsigned nb[L::Q];
-    if constexpr (PR == 2 && std::is_same_v<MR, MrStaged<FT>>) {
+    if constexpr (PR == 2 && !PERIODIC && std::is_same_v<MR, MrStaged<FT>>) {
         // the mixed multirange collide is held to 168 registers: with the
         // neighbours' coordinates shared it spilled 16 of them off periodic
-        // boxes, direction by direction it fits in 140
+        // boxes, direction by direction it fits in 140 (224 x 176 x 79 with
+        // walls and outflow 526 us a step, 474; periodic, where nothing
+        // spills, shared ones are 7 % the faster)
 #pragma unroll
         for (int i = 1; i < L::Q; ++i) nb[i] = (unsigned)stencil_node<L>(P, x, y, z, i);
     } else {
