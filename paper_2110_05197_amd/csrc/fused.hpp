@@ -563,7 +563,7 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 }
 
 // One-pass kernels that keep 64-bit addressing below the 4 GB line too
-// (KParams::far_rows), from sweeps of 1500 random boxes stepped both ways; t is
+// (KParams::far_rows), from sweeps of 1600 random boxes stepped both ways; t is
 // the time through buffers over the time through pointers (10 % quantile,
 // median, 90 % quantile).
 // - FP16 storage with walls or outflow: t 0.99, 1.02, 1.06 on D3Q19, 1.01, 1.02,
@@ -572,8 +572,10 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 //   (periodic 0.94, 0.96, 0.98), and FP32 with two components, t 0.99, 1.005, 1.02,
 //   up to 1.17 (one component 0.99, 0.99, 1.00; FP64 0.96, 0.99, 1.01).
 // - D3Q19 on 96-wide columns, periodic: the Shan-Chen models in FP32, t 1.00, 1.03,
-//   1.05 (every other FP32 box 0.90, 0.97, 1.01, with rows on the cache lines or off
-//   them), the two-component one in FP16 storage too (1.01, 1.04, 1.08).
+//   1.05, the two-component one in FP16 storage too (1.01, 1.04, 1.08).
+// - D3Q19 FP32 colour gradient, periodic, more than one column and rows off the
+//   cache lines, from 2^22 nodes: t 0.98, 1.02, 1.06 (178 x 192 x 140 434 and 473 us;
+//   fewer nodes 0.93, 0.98, 1.04, every other FP32 box 0.90, 0.97, 1.01).
 // - D3Q19 mixed, with the mass-keeping collision, periodic, more than one column
 //   and rows off the cache lines: t 0.97, 1.01, 1.05 (else 0.95, 0.98, 1.01).
 // - D3Q19 FP64, two components, from 11 * 2^20 nodes: t 0.97, 1.07, 1.15 (8 to
@@ -585,8 +587,9 @@ inline bool column_pointers(const KParams &P, bool flat, int precision, int mode
     const bool wide = P.nx % 96 == 0 && P.nx % 64 != 0;
     if (precision == 3) return !periodic || (!flat && wide && model == SC_MC);
     if (flat) return (precision == 1 && model != SC_MP) || (precision == 2 && model == CG && !periodic);
-    if (precision == 1) return model != CG && wide && periodic;
-    if (precision == 2) return P.conserve && periodic && P.nx > 64 && P.nx % 32 != 0;
+    const bool off_lines = P.nx > 64 && P.nx % 32 != 0;
+    if (precision == 1) return periodic && (model != CG ? wide : off_lines && P.N >= 1 << 22);
+    if (precision == 2) return P.conserve && periodic && off_lines;
     return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
 }
 
@@ -667,18 +670,22 @@ inline bool fused_shape(const KParams &P, FusedShape &sh, int precision)
 
 // Automatic choice between the one-pass and the two-pass kernels on D3Q19,
 // where both exist: two-pass where the one-pass shape's overhead is past a line.
-// The lines come from 1100 random boxes of 24 to 350 nodes a side in every
+// The lines come from 1900 random boxes of 24 to 350 nodes a side in every
 // precision and model, a third of them periodic, stepped both ways.  Median
 // one-pass over two-pass time at an overhead of 1.15-1.3, 1.3-1.5 and 2-3:
 //   FP64 CG 0.87, 1.03, 1.45       mixed CG 0.92, 1.02, 1.43
 //   FP32 CG 0.84, 1.07, 1.23       FP32 SC_MP 0.87, 1.11, 1.32
 //   FP32 SC_MC 1.04, 0.9-1.1, 1.32  mixed SC_MP 1.02, 1.12, 1.36
 //   FP16 CG 0.96, 1.03, 1.13       FP16 SC_MP 1.5, 1.5, 1.5
-// and of the mass-keeping collision alike.  64 x 4 columns below FP64 hold half
-// the waves of 64 x 8 ones and break even under 1.3, 96-wide ones at 1.35-1.45 for
-// the colour gradient and 1.2 else.  Of 476 further boxes 17 are left the choice
-// that takes more than 5 % longer, by 37 % at most (FP16 boxes of 10^5 nodes among
-// them, 10 to 20 us either way).  Up to 2^13 nodes a step takes 6-12 us either way.
+// and of the mass-keeping collision alike.  FP64 with two components breaks even
+// at 1.45 with walls and 1.6 periodic (110 x 104 x 117 CG, 1.58: 245 us and 279), FP32
+// with two components, periodic, at 1.62 where one population buffer fits the
+// Infinity Cache and both do not (52 x 216 x 124 CG, 1.58: 112 and 151), 64 x 4
+// columns below FP64, which hold half the waves of 64 x 8 ones, under 1.3, 96-wide
+// ones at 1.35-1.45 for the colour gradient and 1.2 else.  One box in 25 is left the
+// choice that takes more than 5 % longer, by 37 % at most (FP16 boxes of 10^5 nodes
+// among them, 10 to 20 us either way).  Up to 2^13 nodes a step takes 6-12 us either
+// way.
 inline double one_pass_line(const KParams &P, const FusedShape &sh, int precision, int model)
 {
     const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
@@ -686,7 +693,11 @@ inline double one_pass_line(const KParams &P, const FusedShape &sh, int precisio
     if (precision == 3 ? low || model == SC_MP : low && model == SC_MP) return 1.1;
     if (low) return 1.25;
     if (sh.tx == 96) return precision != 3 && model == CG ? 1.47 : 1.2;
+    // bytes of both population buffers, against the 256 MB Infinity Cache
+    const double state = 76.0 * (model == SC_MP ? 1 : 2) * (precision == 0 ? 8 : precision == 3 ? 2 : 4) / 2.0 * (double)P.N;
+    if (precision == 0) return !periodic ? (model == SC_MP ? 1.4 : 1.45) : model == SC_MP && state < 0x1p28 ? 1.35 : 1.6;
     if (model == SC_MP) return periodic ? 1.35 : 1.25;
+    if (precision == 1 && periodic && state > 0x1p28 && state < 0x1p29) return 1.62;
     return periodic ? 1.45 : 1.4;
 }
 inline bool d3_prefers_two_pass(const KParams &P, int precision, int model)
