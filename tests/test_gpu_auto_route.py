@@ -122,3 +122,34 @@ def test_batched_kernel_left_to_the_automatic_choice(M, model, precision, box, b
         out.append(s.export_f())
         s.close()
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("lattice,box", [("D3Q19", (128, 112, 96)), ("D2Q9", (700, 700, 1))])
+def test_diverged_states_step_in_the_same_time(M, lattice, box):
+    """A state that is bad at every node flags it once, not once per wavefront:
+    two-pass steps take no more than 1.5 times those of a sound state (3 times
+    with an atomic from every wavefront), and the flag is set."""
+    import torch
+    nx, ny, nz = box
+    p = M.make_params(lattice=getattr(M, lattice), model=M.SC_MP, precision=M.FP32, nx=nx, ny=ny, nz=nz, G=-5.0,
+                      rho0_R=1.9, rho0_B=0.12, kernel=M.KERNEL_TWO_PASS)
+    us = []
+    for bad in (False, True):
+        s = M.Sim(p)
+        s.init_equilibrium(*fields(M, "SC_MP", (nz, ny, nx)))
+        if bad:
+            s.import_f(torch.full_like(s.export_f(), float("nan")))
+        s.step(4)
+        t = []
+        for _ in range(7):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            s.step(20)
+            e[1].record()
+            e[1].synchronize()
+            t.append(e[0].elapsed_time(e[1]) / 20 * 1e3)
+        us.append(min(t))
+        assert s.diverged() == bad
+        s.close()
+    print(f"[diverged] {lattice} {box} sound {us[0]:.1f} diverged {us[1]:.1f} us", flush=True)
+    assert us[1] <= 1.5 * us[0]
