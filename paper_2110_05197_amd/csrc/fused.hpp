@@ -143,11 +143,15 @@ template <int PR, bool YH> constexpr bool kPointerLoads = (PR == 1 && !YH) || (P
 
 // The type of a column's node indices (N < 2^31).  With 32-bit indices the
 // pointer loads hold a zero-extended copy beside each offset: mixed-precision
-// columns, at the 256 registers an eight-wave block allows, spilled 3-47 of them
-// in the periodic kernels that hold 64-bit ones without (2-4 with the
-// mass-keeping collision on ragged rows), and boxes in the other precisions
-// took 0-3 % longer.
-using ColumnIndex = long long;
+// columns, at the 256 registers an eight-wave block allows, then spill 12-47 of
+// them with the mass-keeping collision, where 64-bit ones spill 0-4 (0.68-0.84 of
+// the time), 96-wide ones 3 instead of none (0.94-1.0), and boxes in the other
+// precisions take 0-3 % longer.  The plain mixed colour gradient on 64-wide
+// periodic columns is the exception: it spills 4-25 with 32-bit indices and is 2-13 %
+// faster for them (256^3 1116 us and 1204, 213 x 136 x 197 0.89 and 1.01 of the time
+// through plain pointers), for the order its loads then leave in.
+template <int PR, int MODEL, int TX, bool PERIODIC, int CONS>
+using ColumnIndex = std::conditional_t<PR == 2 && MODEL == CG && TX == 64 && PERIODIC && CONS == kConsNever, unsigned, long long>;
 
 // One block's work: the TX x TY column at (x0, y0), planes [z0, z1).  An
 // EDGE column is the last one in x when TX does not divide nx: its first
@@ -207,7 +211,7 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
     const int h_slot = (hy + RY) * HX + (hx + 1);
     const int hgx = stencil_coord(x0 + hx, nx, P.bc[0]);
     const int hgy = stencil_coord(y0 + hy, ny, P.bc[1]);
-    using Idx = ColumnIndex;
+    using Idx = ColumnIndex<PR, MODEL, TX, PERIODIC, CONS>;
     const Idx n_xy = (Idx)x + (Idx)nx * (Idx)y;
     const Idx h_xy = (Idx)hgx + (Idx)nx * (Idx)hgy;
     const Idx sxy = (Idx)nx * (Idx)ny;
@@ -576,8 +580,9 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 // - D3Q19 FP32 colour gradient, periodic, more than one column and rows off the
 //   cache lines, from 2^22 nodes: t 0.98, 1.02, 1.06 (178 x 192 x 140 434 and 473 us;
 //   fewer nodes 0.93, 0.98, 1.04, every other FP32 box 0.90, 0.97, 1.01).
-// - D3Q19 mixed, with the mass-keeping collision, periodic, more than one column
-//   and rows off the cache lines: t 0.97, 1.01, 1.05 (else 0.95, 0.98, 1.01).
+// - D3Q19 mixed colour gradient, periodic, more than one column and rows off the
+//   cache lines: with the mass-keeping collision t 0.97, 1.01, 1.05, without 1.06 at
+//   the median (the other models 0.95, 0.98, 1.01).
 // - D3Q19 FP64, two components, from 11 * 2^20 nodes: t 0.97, 1.07, 1.15 (8 to
 //   11 * 2^20 nodes 0.95, 0.98, 1.03, fewer 0.90, 0.94, 0.98); not the colour
 //   gradient on ragged rows with walls (0.90, 0.94, 0.96 at any size).
@@ -589,7 +594,7 @@ inline bool column_pointers(const KParams &P, bool flat, int precision, int mode
     if (flat) return (precision == 1 && model != SC_MP) || (precision == 2 && model == CG && !periodic);
     const bool off_lines = P.nx > 64 && P.nx % 32 != 0;
     if (precision == 1) return periodic && (model != CG ? wide : off_lines && P.N >= 1 << 22);
-    if (precision == 2) return P.conserve && periodic && off_lines;
+    if (precision == 2) return model == CG && periodic && off_lines;
     return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
 }
 

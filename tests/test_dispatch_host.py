@@ -56,7 +56,7 @@ def test_addressing_of_the_one_pass_kernels(ask):
     """Buffer accesses unless the box is one of those that pointers serve better."""
     near = [(1, CG, FP32, (234, 80, 119), PERIODIC, 0), (1, CG, FP32, (141, 72, 164), PERIODIC, 0),
             (1, CG, FP32, (57, 192, 239), WALLS, 0), (1, SC_MC, FP32, (110, 136, 217), WALLS, 0),
-            (1, CG, MIXED, (113, 48, 155), PERIODIC, 0), (1, CG, MIXED, (234, 80, 120), WALLS, 1),
+            (1, SC_MC, MIXED, (113, 48, 155), PERIODIC, 0), (1, CG, MIXED, (234, 80, 120), WALLS, 1),
             (1, CG, MIXED, (96, 96, 384), WALLS, 0), (1, CG, FP64, (223, 224, 183), WALLS, 0),
             (1, CG, FP64, (208, 336, 331), WALLS, 0), (1, CG, FP64, (192, 192, 192), PERIODIC, 0),
             (1, SC_MP, FP64, (256, 256, 256), PERIODIC, 0), (1, CG, FP16, (160, 160, 160), PERIODIC, 0),
@@ -65,7 +65,7 @@ def test_addressing_of_the_one_pass_kernels(ask):
             (0, CG, FP64, (1900, 1100, 1), (0, 1, 0), 0), (0, SC_MC, MIXED, (1900, 1100, 1), (0, 1, 0), 0)]
     far = [(1, CG, FP32, (178, 192, 140), PERIODIC, 0), (1, CG, FP16, (96, 72, 90), (0, 1, 0), 0), (1, SC_MC, FP16, (58, 112, 115), WALLS, 0),
            (1, SC_MP, FP16, (200, 120, 90), WALLS, 0), (1, SC_MC, FP16, (96, 192, 210), PERIODIC, 0),
-           (1, CG, MIXED, (213, 160, 169), PERIODIC, 1), (1, CG, FP64, (256, 256, 256), PERIODIC, 0),
+           (1, CG, MIXED, (213, 160, 169), PERIODIC, 1), (1, CG, MIXED, (213, 136, 197), PERIODIC, 0), (1, CG, FP64, (256, 256, 256), PERIODIC, 0),
            (1, SC_MC, FP64, (307, 368, 130), WALLS, 0), (1, CG, FP64, (256, 336, 233), WALLS, 0),
            (1, SC_MP, FP32, (96, 96, 96), PERIODIC, 0), (1, SC_MC, FP32, (96, 136, 201), PERIODIC, 0),
            (0, CG, MIXED, (1900, 1100, 1), (0, 1, 0), 0), (0, CG, FP32, (4096, 4096, 1), PERIODIC, 0),
