@@ -325,7 +325,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=20)
     ap.add_argument("--size", type=int, default=256)
     ap.add_argument("--precision", type=int, default=1, help="0 FP64, 1 FP32, 2 mixed, 3 FP16")
-    ap.add_argument("--kernel", type=int, default=0, help="0 auto (fused), 1 two-pass, 2 fused")
+    ap.add_argument("--kernel", type=int, default=0, help="0 auto (the faster), 1 two-pass, 2 fused")
     ap.add_argument("--cpu-steps", type=int, default=20)
     ap.add_argument("--cpu-steps-one-thread", type=int, default=2)
     ap.add_argument("--no-cpu-baseline", action="store_true")

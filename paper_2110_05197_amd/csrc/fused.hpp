@@ -144,9 +144,9 @@ template <int PR, bool YH> constexpr bool kPointerLoads = (PR == 1 && !YH) || (P
 // The type of a column's node indices (N < 2^31).  With 32-bit indices the
 // pointer loads hold a zero-extended copy beside each offset: mixed-precision
 // columns, at the 256 registers an eight-wave block allows, then spill 12-47 of
-// them with the mass-keeping collision, where 64-bit ones spill 0-4 (0.68-0.84 of
-// the time), 96-wide ones 3 instead of none (0.94-1.0), and boxes in the other
-// precisions take 0-3 % longer.  The plain mixed colour gradient on 64-wide
+// them with the mass-keeping collision on periodic boxes, where 64-bit ones spill
+// 0-4 (0.68-0.84 of the time), 96-wide ones 3 instead of none (0.94-1.0), and boxes
+// in the other precisions take 0-3 % longer.  The plain mixed colour gradient on 64-wide
 // periodic columns is the exception: it spills 4-25 with 32-bit indices and is 2-13 %
 // faster for them (256^3 1116 us and 1204, 213 x 136 x 197 0.89 and 1.01 of the time
 // through plain pointers), for the order its loads then leave in.
@@ -395,7 +395,7 @@ constexpr int batch_ty(int precision) { return precision == 0 || precision == 2 
 // 64-wide split would leave half of its last column empty.  Not FP64, nor the
 // mixed-precision colour gradient: a six-wave block allows 256 registers a
 // lane, and their batched columns (which ask each simulation whether to keep
-// colour mass) need more (FP64 about 400; mixed 40 spilled).
+// colour mass) need more (FP64 about 400, mixed 290).
 constexpr int kBatchWideTX = 96, kBatchWideTY = 4;
 constexpr bool batch_wide_kernel(int precision, int model)
 {

@@ -92,8 +92,7 @@ __device__ __forceinline__ void stage_box(const KParams &P, const FT *__restrict
 // Waves per SIMD the multirange collide is compiled for.  FP32 fits four with 4
 // registers spilled (256^3 step 1.99 ms, collide 1.43; with 64-bit addressing
 // a dozen spilled, 2.06 and 1.53, and 2.19 at the three waves the compiler
-// chose).  Mixed fits three (its periodic instance without spilling, the other
-// with 16), FP16 storage three and FP64 two, both without spilling.
+// chose).  Mixed and FP16 storage fit three and FP64 two, without spilling.
 template <int PR> constexpr int kMrWaves = PR == 1 ? 4 : PR == 0 ? 2 : 3;
 
 // Collide pass of the multirange two-component Shan-Chen step (D3Q19): a
