@@ -577,6 +577,10 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 //   up to 1.17 (one component 0.99, 0.99, 1.00; FP64 0.96, 0.99, 1.01).
 // - D3Q19 on 96-wide columns, periodic: the Shan-Chen models in FP32, t 1.00, 1.03,
 //   1.05, the two-component one in FP16 storage too (1.01, 1.04, 1.08).
+// - D3Q19 FP32 on 96-wide columns with walls or outflow, two components, from 2^19
+//   nodes: colour gradient t 1.00, 1.02, 1.04, Shan-Chen 1.00, 1.05, 1.07 (fewer nodes
+//   0.95-1.03; one component 0.98, 1.00, 1.01; the colour gradient periodic 0.92, 0.985,
+//   1.005; 96 x 96 x 384 319 us, 309 through pointers).
 // - D3Q19 FP32 colour gradient, periodic, more than one column and rows off the
 //   cache lines, from 2^22 nodes: t 0.98, 1.02, 1.06 (178 x 192 x 140 434 and 473 us;
 //   fewer nodes 0.93, 0.98, 1.04, every other FP32 box 0.90, 0.97, 1.01).
@@ -593,7 +597,10 @@ inline bool column_pointers(const KParams &P, bool flat, int precision, int mode
     if (precision == 3) return !periodic || (!flat && wide && model == SC_MC);
     if (flat) return (precision == 1 && model != SC_MP) || (precision == 2 && model == CG && !periodic);
     const bool off_lines = P.nx > 64 && P.nx % 32 != 0;
-    if (precision == 1) return periodic && (model != CG ? wide : off_lines && P.N >= 1 << 22);
+    if (precision == 1) {
+        if (!periodic) return wide && model != SC_MP && P.N >= 1 << 19;
+        return model != CG ? wide : off_lines && P.N >= 1 << 22;
+    }
     if (precision == 2) return model == CG && periodic && off_lines;
     return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
 }

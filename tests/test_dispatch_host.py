@@ -60,6 +60,7 @@ def test_addressing_of_the_one_pass_kernels(ask):
             (1, CG, MIXED, (96, 96, 384), WALLS, 0), (1, CG, FP64, (223, 224, 183), WALLS, 0),
             (1, CG, FP64, (208, 336, 331), WALLS, 0), (1, CG, FP64, (192, 192, 192), PERIODIC, 0),
             (1, SC_MP, FP64, (256, 256, 256), PERIODIC, 0), (1, CG, FP16, (160, 160, 160), PERIODIC, 0),
+            (1, CG, FP32, (96, 40, 77), WALLS, 0), (1, SC_MP, FP32, (96, 208, 259), WALLS, 0),
             (1, SC_MP, FP32, (96, 96, 96), WALLS, 0), (1, CG, FP32, (96, 96, 96), PERIODIC, 0),
             (0, CG, MIXED, (1900, 1100, 1), PERIODIC, 0), (0, SC_MP, FP32, (1900, 1100, 1), PERIODIC, 0),
             (0, CG, FP64, (1900, 1100, 1), (0, 1, 0), 0), (0, SC_MC, MIXED, (1900, 1100, 1), (0, 1, 0), 0)]
@@ -67,6 +68,7 @@ def test_addressing_of_the_one_pass_kernels(ask):
            (1, SC_MP, FP16, (200, 120, 90), WALLS, 0), (1, SC_MC, FP16, (96, 192, 210), PERIODIC, 0),
            (1, CG, MIXED, (213, 160, 169), PERIODIC, 1), (1, CG, MIXED, (213, 136, 197), PERIODIC, 0), (1, CG, FP64, (256, 256, 256), PERIODIC, 0),
            (1, SC_MC, FP64, (307, 368, 130), WALLS, 0), (1, CG, FP64, (256, 336, 233), WALLS, 0),
+           (1, CG, FP32, (96, 96, 384), WALLS, 0), (1, SC_MC, FP32, (288, 72, 127), (1, 1, 1), 0),
            (1, SC_MP, FP32, (96, 96, 96), PERIODIC, 0), (1, SC_MC, FP32, (96, 136, 201), PERIODIC, 0),
            (0, CG, MIXED, (1900, 1100, 1), (0, 1, 0), 0), (0, CG, FP32, (4096, 4096, 1), PERIODIC, 0),
            (0, CG, FP16, (1900, 1100, 1), (0, 1, 0), 0)]
