@@ -265,16 +265,20 @@ __device__ __forceinline__ void fused_column(const KParams &P, const void *srcp,
         // SIMD's other waves take the issue slots for their arithmetic: 2-D
         // rows 4096^2 FP32 0.489 -> 0.480 ms, buffer loads at 256^3 FP32 1.155
         // -> 1.085 ms, 64-bit addressed columns on ragged rows 234 x 80 x 119
-        // FP32 0.223 -> 0.217.
+        // FP32 0.223 -> 0.217.  In the other precisions it is worth -2 to +4 %
+        // (150 boxes of nine shapes; one component in mixed precision and FP16
+        // storage gains most, 192^3 295 -> 284 us; FP64 within 1 %), but periodic
+        // mixed two-component Shan-Chen boxes lose 1-7 % (160^3 316 -> 334 us).
+        constexpr bool raised = !(PR == 2 && MODEL == SC_MC);
         constexpr int spacing = FAR || !SPREAD ? 0 : kLoadSpacing<PR, MODEL, YH>;
         const bool ahead = z + 2 <= z1;
         RawNode<L, K, S, C> dr_, hr_;
-        __builtin_amdgcn_s_setprio(3);
+        if constexpr (raised) __builtin_amdgcn_s_setprio(3);
         if (ahead) {
             if (spacing == 0 && act) dr_.load(src, n_xy + zoff(z + 2));
             if (has_h) hr_.load(src, h_xy + zoff(z + 2));
         }
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (raised) __builtin_amdgcn_s_setprio(0);
 
         // 2. collide plane z with the stencil values of planes z-1, z, z+1
         if (act) {
