@@ -571,7 +571,7 @@ void launch_batch_fused(SimDesc *D, int n, long long fblocks, int kinds, hipStre
 }
 
 // One-pass kernels that keep 64-bit addressing below the 4 GB line too
-// (KParams::far_rows), from sweeps of 1600 random boxes stepped both ways; t is
+// (KParams::far_rows), from sweeps of 1800 random boxes stepped both ways; t is
 // the time through buffers over the time through pointers (10 % quantile,
 // median, 90 % quantile).
 // - FP16 storage with walls or outflow: t 0.99, 1.02, 1.06 on D3Q19, 1.01, 1.02,
@@ -607,6 +607,19 @@ inline bool column_pointers(const KParams &P, bool flat, int precision, int mode
     }
     if (precision == 2) return model == CG && periodic && off_lines;
     return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
+}
+
+// The same for a batched one-pass step, whose launches hold several simulations.
+// Periodic, of 1-8 equal boxes: also the colour gradient on 96-wide columns, in FP32
+// (70 batches, t 0.98, 1.025, 1.045) and FP16 storage (1.00, 1.07, 1.12), and FP32 SC
+// multiphase with edge columns (50 batches, 1.00, 1.035, 1.06; whole ones 0.99).
+inline bool batch_column_pointers(const KParams &P, int precision, int model)
+{
+    const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
+    const bool wide = batch_wide(precision, model, P.nx, P.ny);
+    if (periodic && wide && model == CG && (precision == 1 || precision == 3)) return true;
+    if (periodic && model == SC_MP && precision == 1 && P.nx % kBatchTX != 0) return true;
+    return column_pointers(P, false, precision, model);
 }
 
 // A box's columns (D3Q19) on the one-pass kernel, planned once per simulation.

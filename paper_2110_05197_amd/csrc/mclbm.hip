@@ -1085,6 +1085,7 @@ mclbm_status mclbm_batch_create(mclbm_sim *const *sims, int32_t n, const int64_t
             d.block0 = g.blocks;
             d.fblock0 = g.fblocks;
             if (batch_fused_ok(s->prm, resident)) {
+                d.P.far_rows = d.P.far || batch_column_pointers(d.P, s->prm.precision, s->prm.model) ? 1 : 0;
                 d.ftz = batch_fused_tz(s->prm.nz, group_tz);
                 d.fnblocks = batch_fused_columns(s->prm) * ((s->prm.nz + d.ftz - 1) / d.ftz);
                 g.fblocks += d.fnblocks;
@@ -1092,7 +1093,7 @@ mclbm_status mclbm_batch_create(mclbm_sim *const *sims, int32_t n, const int64_t
                                       && s->prm.bc[2] == MCLBM_PERIODIC;
                 g.fused_kinds |= fused_kind(periodic, s->prm.nx % kBatchTX != 0,
                                             batch_wide(s->prm.precision, s->prm.model, s->prm.nx, s->prm.ny),
-                                            s->kp.far_rows != 0);
+                                            d.P.far_rows != 0);
             } else {
                 d.nblocks = grid_of(s->kp.N);
                 g.blocks += d.nblocks;
