@@ -144,7 +144,8 @@ bool auto_prefers_fused(const mclbm_params &p)
 // Batches left to the automatic choice, boxes of 2^16 nodes up (FP64: 2^17):
 // classes whose batched one-pass step is the slower.  One-pass over two-pass time
 // of batches of 1-8 equal boxes, 700 of them (least, median, most): mixed CG 0.98,
-// 1.3, 1.8, SC_MP with walls or wider than 96 1.1, 1.35, 1.7 (else 0.83-1.18), SC_MC
+// 1.3, 1.8, SC_MP with walls or wider than 96 1.1, 1.35, 1.7 (else 0.83-1.18; periodic
+// on 96-wide columns, 14 batches, 0.97-1.35 up to 1.5 * 2^20 nodes, 0.89-0.99 above), SC_MC
 // likewise 0.98, 1.3, 1.6 (else 0.85-1.2, on 96-wide columns 0.71-0.87); FP16 SC_MP
 // 0.93, 1.4, 1.8, SC_MC 0.93, 1.15, 1.4 (64 wide, periodic, 0.97-1.03), CG with walls
 // 1.03, 1.15, 1.3; with walls also FP32 SC_MP 1.02, 1.2, 1.4 and FP64 CG 1.04, 1.1,
@@ -152,11 +153,14 @@ bool auto_prefers_fused(const mclbm_params &p)
 bool batch_two_pass_faster(const mclbm_params &p)
 {
     const long long least = p.precision == MCLBM_FP64 ? 1 << 17 : 1 << 16;
-    if (p.kernel != MCLBM_KERNEL_AUTO || (long long)p.nx * p.ny * p.nz < least) return false;
+    const long long N = (long long)p.nx * p.ny * p.nz;
+    if (p.kernel != MCLBM_KERNEL_AUTO || N < least) return false;
     const bool periodic = p.bc[0] == MCLBM_PERIODIC && p.bc[1] == MCLBM_PERIODIC && p.bc[2] == MCLBM_PERIODIC;
     const bool wide = batch_wide(p.precision, p.model, p.nx, p.ny);
     switch (p.precision) {
-    case MCLBM_MIXED: return p.model == MCLBM_CG || ((!periodic || p.nx > 96) && !(p.model == MCLBM_SC_MC && wide));
+    case MCLBM_MIXED:
+        return p.model == MCLBM_CG || (p.model == MCLBM_SC_MC && (!periodic || p.nx > 96) && !wide)
+               || (p.model == MCLBM_SC_MP && (!periodic || (p.nx > 96 && !(wide && N >= 3 << 19))));
     case MCLBM_FP16: return p.model == MCLBM_SC_MP || !periodic || (p.model == MCLBM_SC_MC && p.nx != 64);
     case MCLBM_FP32: return p.model == MCLBM_SC_MP && !periodic;
     default: return p.model == MCLBM_CG && !periodic;

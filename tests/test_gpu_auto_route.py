@@ -99,6 +99,7 @@ def test_columns_of_a_box_left_to_the_automatic_choice(M, lattice, precision, bo
     ("CG", "FP64", (96, 48, 72), (1, 1, 2), "TWO_PASS"), ("SC_MP", "FP32", (96, 80, 44), (1, 1, 2), "TWO_PASS"),
     ("CG", "FP32", (96, 64, 56), (0, 0, 0), "FUSED"), ("SC_MC", "MIXED", (96, 72, 127), (0, 0, 0), "FUSED"),
     ("CG", "FP64", (64, 64, 66), (0, 0, 0), "FUSED"), ("SC_MP", "FP32", (64, 136, 40), (0, 0, 0), "FUSED"),
+    ("SC_MP", "MIXED", (288, 56, 98), (0, 0, 0), "FUSED"), ("SC_MP", "MIXED", (288, 48, 72), (0, 0, 0), "TWO_PASS"),
     ("CG", "FP16", (96, 48, 44), (0, 0, 0), "FUSED"), ("SC_MP", "FP32", (112, 40, 44), (0, 0, 0), "FUSED"),
     ("CG", "MIXED", (128, 16, 16), (0, 0, 0), "FUSED")])
 def test_batched_kernel_left_to_the_automatic_choice(M, model, precision, box, bc, kernel):
