@@ -500,6 +500,23 @@ inline int batch_group_tz(const long long *cols, const int *nz, int n, long long
     return best;
 }
 
+// Classes of one-pass steps that always address through pointers (column_pointers
+// has the times), which need no kernels with buffer accesses: rows of D2Q9 (flat),
+// 96-wide columns or others.
+constexpr bool always_pointers(int precision, int model, bool periodic, bool flat, bool wide)
+{
+    if (precision == 3) return !periodic || (!flat && wide && model == SC_MC);
+    if (flat) return (precision == 1 && model != SC_MP) || (precision == 2 && model == CG && !periodic);
+    return precision == 1 && periodic && model != CG && wide;
+}
+// The same of the batched kernels (batch_column_pointers).
+constexpr bool batch_always_pointers(int precision, int model, bool periodic, bool edge, bool wide)
+{
+    if (periodic && wide && model == CG && (precision == 1 || precision == 3)) return true;
+    if (periodic && edge && model == SC_MP && precision == 1) return true;
+    return always_pointers(precision, model, periodic, false, wide);
+}
+
 // Blocks a compute unit holds of the batched one-pass kernels of one column
 // width: the fewest over periodic or not, edge columns or not, near and FAR.
 template <int PR, int MODEL, bool WIDE>
@@ -507,10 +524,12 @@ int batch_fused_per_cu()
 {
     constexpr int lds = fused_lds_bytes<PR, MODEL, kb_tx(WIDE), kb_ty(PR, WIDE)>();
     constexpr bool EDGE = !WIDE;
+    constexpr bool PF = batch_always_pointers(PR, MODEL, true, false, WIDE), BF = batch_always_pointers(PR, MODEL, false, false, WIDE);
+    constexpr bool PE = batch_always_pointers(PR, MODEL, true, EDGE, WIDE), BE = batch_always_pointers(PR, MODEL, false, EDGE, WIDE);
     const void *fns[8] = {
-        (const void *)kb_fused<PR, MODEL, true, false, WIDE, false>, (const void *)kb_fused<PR, MODEL, false, false, WIDE, false>,
+        (const void *)kb_fused<PR, MODEL, true, false, WIDE, PF>, (const void *)kb_fused<PR, MODEL, false, false, WIDE, BF>,
         (const void *)kb_fused<PR, MODEL, true, false, WIDE, true>, (const void *)kb_fused<PR, MODEL, false, false, WIDE, true>,
-        (const void *)kb_fused<PR, MODEL, true, EDGE, WIDE, false>, (const void *)kb_fused<PR, MODEL, false, EDGE, WIDE, false>,
+        (const void *)kb_fused<PR, MODEL, true, EDGE, WIDE, PE>, (const void *)kb_fused<PR, MODEL, false, EDGE, WIDE, BE>,
         (const void *)kb_fused<PR, MODEL, true, EDGE, WIDE, true>, (const void *)kb_fused<PR, MODEL, false, EDGE, WIDE, true>};
     int per_cu = 1 << 30;
     for (int i = 0; i < (EDGE ? 8 : 4); ++i) {
@@ -541,15 +560,17 @@ long long batch_fused_resident()
 template <int PR, int MODEL, bool PERIODIC, bool EDGE, bool WIDE, bool FAR>
 void launch_batch_kind(SimDesc *D, int n, long long fblocks, int kinds, hipStream_t s)
 {
-    if (!(kinds & fused_kind(PERIODIC, EDGE, WIDE, FAR))) return;
-    constexpr int TX = kb_tx(WIDE), TY = kb_ty(PR, WIDE), lds = fused_lds_bytes<PR, MODEL, TX, TY>();
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)kb_fused<PR, MODEL, PERIODIC, EDGE, WIDE, FAR>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr_set = true;
+    if constexpr (FAR || !batch_always_pointers(PR, MODEL, PERIODIC, EDGE, WIDE)) {
+        if (!(kinds & fused_kind(PERIODIC, EDGE, WIDE, FAR))) return;
+        constexpr int TX = kb_tx(WIDE), TY = kb_ty(PR, WIDE), lds = fused_lds_bytes<PR, MODEL, TX, TY>();
+        static bool attr_set = false;
+        if (!attr_set) {
+            (void)hipFuncSetAttribute((const void *)kb_fused<PR, MODEL, PERIODIC, EDGE, WIDE, FAR>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            attr_set = true;
+        }
+        hipLaunchKernelGGL((kb_fused<PR, MODEL, PERIODIC, EDGE, WIDE, FAR>), dim3((unsigned)fblocks), dim3(TX * TY), lds, s, D, n);
     }
-    hipLaunchKernelGGL((kb_fused<PR, MODEL, PERIODIC, EDGE, WIDE, FAR>), dim3((unsigned)fblocks), dim3(TX * TY), lds, s, D, n);
 }
 template <int PR, int MODEL, bool FAR>
 void launch_batch_kinds(SimDesc *D, int n, long long fblocks, int kinds, hipStream_t s)
@@ -598,12 +619,12 @@ inline bool column_pointers(const KParams &P, bool flat, int precision, int mode
 {
     const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
     const bool wide = P.nx % 96 == 0 && P.nx % 64 != 0;
-    if (precision == 3) return !periodic || (!flat && wide && model == SC_MC);
-    if (flat) return (precision == 1 && model != SC_MP) || (precision == 2 && model == CG && !periodic);
+    if (always_pointers(precision, model, periodic, flat, wide)) return true;
+    if (flat || precision == 3) return false;
     const bool off_lines = P.nx > 64 && P.nx % 32 != 0;
     if (precision == 1) {
         if (!periodic) return wide && model != SC_MP && P.N >= 1 << 19;
-        return model != CG ? wide : off_lines && P.N >= 1 << 22;
+        return model == CG && off_lines && P.N >= 1 << 22;
     }
     if (precision == 2) return model == CG && periodic && off_lines;
     return model != SC_MP && P.N >= 11LL << 20 && (periodic || model != CG || P.nx % 64 == 0);
@@ -617,9 +638,8 @@ inline bool batch_column_pointers(const KParams &P, int precision, int model)
 {
     const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
     const bool wide = batch_wide(precision, model, P.nx, P.ny);
-    if (periodic && wide && model == CG && (precision == 1 || precision == 3)) return true;
-    if (periodic && model == SC_MP && precision == 1 && P.nx % kBatchTX != 0) return true;
-    return column_pointers(P, false, precision, model);
+    return batch_always_pointers(precision, model, periodic, !wide && P.nx % kBatchTX != 0, wide)
+           || column_pointers(P, false, precision, model);
 }
 
 // A box's columns (D3Q19) on the one-pass kernel, planned once per simulation.
@@ -769,19 +789,26 @@ void launch_fused_one(const KParams &P, const void *src, void *dst, unsigned *fl
     hipLaunchKernelGGL((k_fused<PR, MODEL, TX, TY, PERIODIC, COLS, L, LA, CONS, FAR>), grid, block, lds, s, P, src, dst,
                        flag, tz, tiles_x, tiles_y);
 }
+template <int PR, int MODEL, int TX, int TY, bool PERIODIC, int COLS, class L, class LA, bool CONS>
+void launch_fused_far(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, int tiles_x, int tiles_y,
+                      hipStream_t s)
+{
+    if constexpr (!always_pointers(PR, MODEL, PERIODIC, std::is_same_v<L, D2Q9>, TX == 96)) {
+        if (!P.far_rows) {
+            launch_fused_one<PR, MODEL, TX, TY, PERIODIC, COLS, L, LA, CONS, false>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+            return;
+        }
+    }
+    launch_fused_one<PR, MODEL, TX, TY, PERIODIC, COLS, L, LA, CONS, true>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+}
 template <int PR, int MODEL, int TX, int TY, int COLS, class L, class LA, bool CONS>
 void launch_fused_bc(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, int tiles_x, int tiles_y,
                      hipStream_t s)
 {
-    const bool periodic = P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0;
-    if (periodic && !P.far_rows)
-        launch_fused_one<PR, MODEL, TX, TY, true, COLS, L, LA, CONS, false>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
-    else if (periodic)
-        launch_fused_one<PR, MODEL, TX, TY, true, COLS, L, LA, CONS, true>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
-    else if (!P.far_rows)
-        launch_fused_one<PR, MODEL, TX, TY, false, COLS, L, LA, CONS, false>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+    if (P.bc[0] == 0 && P.bc[1] == 0 && P.bc[2] == 0)
+        launch_fused_far<PR, MODEL, TX, TY, true, COLS, L, LA, CONS>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
     else
-        launch_fused_one<PR, MODEL, TX, TY, false, COLS, L, LA, CONS, true>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
+        launch_fused_far<PR, MODEL, TX, TY, false, COLS, L, LA, CONS>(P, src, dst, flag, tz, tiles_x, tiles_y, s);
 }
 template <int PR, int MODEL, int TX, int TY, int COLS, bool CONS>
 void launch_fused_kernel(const KParams &P, const void *src, void *dst, unsigned *flag, int tz, hipStream_t s)
